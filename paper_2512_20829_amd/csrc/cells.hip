@@ -158,9 +158,11 @@ struct BucketKey {
                     const double lw = plo - floor((plo - g.lo[a]) / g.L[a]) * g.L[a];
                     const double hw = phi - floor((phi - g.lo[a]) / g.L[a]) * g.L[a];
                     const int blo = bucket_of(e, nb, lw), bhi = bucket_of(e, nb, hw);
+                    // where the support wraps, its end can lie in the home
+                    // bucket again, one turn away
                     int dl = hb[a] - blo, dr = bhi - hb[a];
-                    dl = dl < 0 ? dl + nb : dl;
-                    dr = dr < 0 ? dr + nb : dr;
+                    dl = dl < 0 || (dl == 0 && lw > xw) ? dl + nb : dl;
+                    dr = dr < 0 || (dr == 0 && hw < xw) ? dr + nb : dr;
                     ra = dl > dr ? dl : dr;
                 }
             } else {

@@ -94,9 +94,11 @@ struct LatticeKey {
                 } else if (ihi - ilo + 1 >= m.n[a]) {
                     ra = m.nt[a];
                 } else {
+                    // the support spans less than a period; where it wraps, its
+                    // end can lie in the home tile again, one turn away
                     int64_t tl = posmod(ilo, m.n[a]) / TE, tr = posmod(ihi, m.n[a]) / TE;
-                    int64_t dl = ilo > hc ? 0 : posmod(ht[a] - tl, m.nt[a]);
-                    int64_t dr = ihi < hc ? 0 : posmod(tr - ht[a], m.nt[a]);
+                    int64_t dl = ilo > hc ? 0 : ht[a] - tl + (ilo < 0 ? m.nt[a] : 0);
+                    int64_t dr = ihi < hc ? 0 : tr - ht[a] + (ihi >= m.n[a] ? m.nt[a] : 0);
                     ra = dl > dr ? dl : dr;
                 }
             } else {
