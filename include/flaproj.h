@@ -297,24 +297,24 @@ fla_status fla_profile_enable(fla_ctx* ctx, int on);
 fla_status fla_profile_read(fla_ctx* ctx, fla_profile* out);
 
 /* Gather plan code: plan + FLA_GATHER_PLANS * shape.
- * The plan is the granularity at which the gather skips the sub-blocks
- * (blocks of 4^3 or 8^2 cells) that a trajectory cannot reach:
+ * The plan is the granularity at which the gather skips the cells that a
+ * trajectory cannot reach.  Binary64 (sub-blocks of 4^3 or 8^2 cells):
  *   0: each sub-block;
- *   1: pairs of sub-blocks along z (3-D, the default; the binary32 loop,
- *      which takes four trajectories per step, adds a test per sub-block);
+ *   1: pairs of sub-blocks along z (3-D, the default);
  *   2, 3: only the workgroup's whole part.
+ * Binary32 in 3-D takes the planes of a tile (8 x 8 cells) for two
+ * trajectories at a time:
+ *   0, 1: two planes; 2: four planes; 3: the whole tile.
  * In 2-D, plans 1-3 skip only the whole tile.
  * The shape is the part of a tile (8^3 or 16^2 cells) one workgroup owns:
- *   0: in 3-D half a tile along x (4 sub-blocks; the default), in 2-D the
- *      whole tile;
- *   1: the whole tile in 3-D (8 sub-blocks: the candidates are scanned and
- *      staged once per tile instead of once per half, with fewer workgroups
- *      per compute unit); not in 2-D.
+ *   0: in binary64 3-D half a tile along x (4 sub-blocks; the default), else
+ *      the whole tile;
+ *   1: the whole tile in 3-D (in binary64 8 sub-blocks: the candidates are
+ *      scanned and staged once per tile instead of once per half, with fewer
+ *      workgroups per compute unit); not in 2-D.
  * So codes 0..7 are valid in 3-D and 0..3 in 2-D.  Under one shape every
  * plan produces the same values (up to the sign of zero); they differ only
- * in speed.  Between shapes, binary64 values are the same as well; binary32
- * values can differ by the rounding of the compensated sums, whose partial
- * sums are folded at other points.  Codes are kept per (dim, prec) in the
+ * in speed.  Between shapes, the values are the same as well.  Codes are kept per (dim, prec) in the
  * context; -1 restores the library default (code 1).
  * Errors: INVALID_ARG for out-of-range arguments. */
 #define FLA_GATHER_PLANS 4

@@ -5,43 +5,42 @@
 // the trajectories of its tile in a fixed order, so results are bitwise
 // reproducible.
 //
-// Work decomposition (one workgroup of four 64-lane waves per part of a tile
-// in 3-D: half the tile, cut across x, by default, or the whole tile; two
-// waves per tile in 2-D; the waves take the candidate chunks in turn and
-// their partial sums are added in wave order at the end; the workgroups are
-// persistent and take their XCD's parts in heaviest-first order, k_gather):
-//  * a tile is TE^D cells, split into 2^D sub-blocks of SB^D cells; lane l
-//    owns the cell with in-block coordinates lc(l) in every sub-block of its
-//    workgroup;
+// Work decomposition: a tile is TE^D cells, a workgroup owns a tile or (3-D,
+// binary64) one half of it across x; the waves of the workgroup (four in
+// 3-D, two in 2-D) take the candidate chunks in turn and their sums are added
+// in wave order at the end; the workgroups are persistent and take their
+// XCD's parts in heaviest-first order (k_gather).
 //  * candidate trajectories come from the buckets (class k, home tile) of
 //    the neighbourhood of the tile: a class-k trajectory reaches at most k
 //    tiles from its home tile (the last class spans whole axes);
 //  * a conservative binary64 sphere/box test compacts candidates into an
 //    LDS list (order preserved with wave ballots);
-//  * per batch of 64 candidates the lanes build, in LDS, the per-axis factors
+//  * per batch of candidates the lanes build, in LDS, the per-axis factors
 //    s = (d/h)^2 and e = exp(-s/2) for the cell centres of the workgroup on
-//    every axis (the Gaussian is separable on a Cartesian mesh), plus the
-//    per-half minima of s, in straight-line code (the minimum image and the
-//    delta records take one branch per axis);
-//  * every lane then walks the batch: a sub-block is visited only if the
-//    minima admit a pair there (an exact, wave-uniform skip); a pair costs
-//    2 adds, 1 compare, 2 multiplies, 1 select and C+1 multiply-adds; in
-//    binary32 the C channel multiply-adds of a sub-block run as one
-//    4x4x1 matrix instruction, and the 3-D plan-1 loop takes four records
-//    per step under the union of their skips (records that reach no cell
-//    of a visited pair of sub-blocks add exact zeros; the unions come from
-//    two lane permutations of the masks);
-//  * binary32 partial sums of one batch are folded into compensated
-//    (TwoSum) totals, binary64 sums need no compensation.
+//    every axis (the Gaussian is separable on a Cartesian mesh), in
+//    straight-line code (the minimum image and the delta records take one
+//    branch per axis);
+//  * every lane then walks the batch over its cells, skipping what a record
+//    reaches nowhere (an exact, wave-uniform skip).
+// Two tile bodies share this frame:
+//  * gather_planes (binary32, 3-D): a lane owns a column of cells, and what
+//    depends on z alone is the same on every lane;
+//  * gather_tile (binary64, and 2-D): the tile is split into 2^D sub-blocks
+//    of SB^D cells and lane l owns the cell with in-block coordinates lc(l)
+//    in every sub-block.
+// Binary32 partial sums run over at most 64 records before they are folded
+// (into binary64 or compensated totals); binary64 sums need no compensation.
 //
-// The tile part a workgroup owns is its shape: half a tile along x (the 3-D
-// default, TP = 2) or the whole tile (TP = 1; always in 2-D).  Plan codes
-// plan + kGatherPlans * shape select both (fla_autotune times them all).
+// Plan codes plan + kGatherPlans * shape (fla_autotune times them all): the
+// plan is the granularity of the skips, the shape the part of a tile that a
+// workgroup owns (in binary32 the whole tile in either shape).
 //
 // This header holds the kernels and their launchers; the units
 // gather_{f32,f64}_{2d,3d}.hip instantiate them per precision and dimension,
 // so that they compile in parallel.
 #pragma once
+#include <type_traits>
+
 #include "internal.hpp"
 #include "kernels.hpp"
 
@@ -87,17 +86,21 @@ __device__ inline void two_sum_acc(R& hi, R& lo, R p)
 // tiles have twice the cells per axis and whose staging tables are larger
 template <int D> struct GatherWaves { static constexpr int value = D == 3 ? 4 : 2; };
 
-// Workgroups per tile (the shape).  With TP = 2 (3-D only) each workgroup
+// Workgroups per tile (the shape).  With TP = 2 (3-D, binary64) each workgroup
 // owns one half of the tile along x (4 of its 8 sub-blocks), which halves
 // the registers of its sums and its staging space, so that more workgroups
 // share a compute unit, at the cost of scanning and staging every candidate
-// once per half.  (Along x: the inclusion sum is ((s_x + s_y) + s_z), so
-// sub-blocks paired along z still share their partial sum s_x + s_y.)
-__host__ __device__ constexpr int tile_parts(int D, int shape) { return D == 3 && shape == 0 ? 2 : 1; }
+// once per half.
+template <typename R> __host__ __device__ constexpr int tile_parts(int D, int shape)
+{
+    return sizeof(R) == 8 && D == 3 && shape == 0 ? 2 : 1;
+}
 
-// Waves per SIMD the register allocation is held to.
+// Waves per SIMD the register allocation is held to (binary32 in 3-D: the
+// sums of eight planes take 120 registers; at three waves the rest spills
+// into the loops, 6.9 instead of 5.0 ms on the 128^3 case).
 template <typename R, int D, int TP> struct GatherOcc {
-    static constexpr int value = sizeof(R) == 4 ? (TP == 2 ? 3 : 2) : 1;
+    static constexpr int value = sizeof(R) == 4 ? 2 : 1;
 };
 
 template <typename R, int D, int TP>
@@ -369,6 +372,560 @@ __device__ __forceinline__ bool candidate_ok(const MeshDev& m, const double4 P, 
     return acc <= filt2;
 }
 
+// ---------------------------------------------------------------------------
+// Binary32, 3-D: whole planes of a tile per wave.
+// ---------------------------------------------------------------------------
+// Lane l owns the column of cells (x, y) = (l % 8, l / 8) of the tile; the
+// eight planes are taken in turn, so that everything that depends on z alone
+// is the same on all 64 lanes:
+//  * the test s_x + s_y + s_z <= c^2 is the comparison of s_x + s_y with a
+//    threshold T(s_z), the largest binary32 t with fl(t + s_z) <= c^2, so the
+//    decision is that of the sum, bit for bit;
+//  * e_z goes into the record's weights (e_z/h, e_z q_k/h), so that a pair's
+//    kernel weight is e_x e_y alone, formed once per record and column.
+// A pair then costs one subtraction (scaled threshold minus scaled s_x + s_y),
+// one median (the weight where the difference is positive, else 0), one
+// multiply-add for the denominator and a quarter of a 4x4x1 matrix
+// instruction for the four channels.  The plane's threshold and denominator
+// weight come out of one register per 16 (record, plane) pairs by a row
+// broadcast inside the vector instruction, the channel weights out of one
+// register by the matrix instruction's own block broadcast: a pair of records
+// costs seven LDS reads for all of its planes.
+constexpr int kPlaneRecs = 2;              // records per register of row broadcasts
+struct PlaneGroup {
+    float2 x[kPlaneRecs][8], y[kPlaneRecs][8];   // {s B, e} at the tile's positions
+    float2 td[kPlaneRecs][8];                    // per plane: scaled threshold, e_z/h
+    float ez[kPlaneRecs][8];
+    float q[kPlaneRecs][4];                      // q_k/h
+};
+struct PlaneLds {
+    static constexpr int NB = 32;          // records per batch (two lanes stage one record)
+    PlaneGroup grp[NB / kPlaneRecs + 1];   // the last one is read ahead, never written or used
+    double4 pos[NB + kWave];               // compacted candidates: position and 1/h,
+    float4 wa[NB + kWave];                 // {1/h, q_0/h, q_1/h, q_2/h}
+    float wb[NB + kWave];                  // and q_3/h
+};
+
+// Home-tile rows of the classes of a tile, in the order they are visited
+// (class by class, row by row, the runs of a row in x order), as one sequence
+// of runs of sorted records.
+struct RunTable {
+    ClassRows cls[kClasses];
+    int base[kClasses + 1];                // first run of each class
+};
+
+// lane j of the row of 16 lanes, on every lane of the row
+template <int J> __device__ __forceinline__ float row_bcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + J, 0xF, 0xF, true));
+}
+
+// Weights of one record in two planes and their part of the denominators:
+// a, b hold scaled threshold minus scaled s_x + s_y and become the kernel
+// weight where that is positive, else 0; the planes' denominator weights are
+// lanes J0 and J1 of each row of dz.  As one block because the compiler does
+// not fold a row broadcast into a multiply-add (a move and a multiply-add
+// instead: one vector instruction in four more); the two medians in front
+// keep the two wait states that a row broadcast needs after any write of dz.
+template <int J0, int J1>
+__device__ __forceinline__ void weigh2(float& a, float& b, const float e, const float dz, float& da, float& db)
+{
+    asm("v_med3_f32 %0, %0, %4, 0\n\t"
+        "v_med3_f32 %1, %1, %4, 0\n\t"
+        "v_fmac_f32_dpp %2, %5, %0 row_newbcast:%c6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %5, %1 row_newbcast:%c7 row_mask:0xf bank_mask:0xf"
+        : "+v"(a), "+v"(b), "+v"(da), "+v"(db)
+        : "v"(e), "v"(dz), "n"(J0), "n"(J1));
+}
+
+template <int I, int N, typename F> __device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// Conservative test of one record against the tile, as candidate_ok but
+// without a branch per axis: the distance to the nearest image of a box centre
+// takes one fold below 5 L / 4 (the margin of filt2 covers its rounding).
+template <bool DELTA>
+__device__ __forceinline__ bool near_tile(const MeshDev& m, const double4 P, const int* tc, const double* bmid,
+                                          const double* bhalf, const bool* faxis, double filt2)
+{
+    const double x[3] = {P.x, P.y, P.z};
+    if (DELTA && P.w < 0.0) {
+        bool ok = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ok = ok && (home_index(m, a, x[a]) / Geo<3>::TE == tc[a]);
+        return ok;
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (!faxis[a]) continue;
+        double d = fabs(bmid[a] - x[a]);
+        if (m.periodic[a]) {
+            if (d > 1.25 * m.L[a]) d = fabs(min_image(d, m.L[a]));
+            d = fmin(d, fabs(d - m.L[a]));
+        }
+        const double u = fmax(d - bhalf[a], 0.0) * P.w;
+        acc = fma(u, u, acc);
+    }
+    return acc <= filt2;
+}
+
+// The work of one workgroup in binary32 and 3-D: one tile.  The four waves
+// take the chunks of 64 candidates in turn and keep their own sums.
+//
+// What bounds it: instruction issue.  A plane of one record takes 22 cycles (a
+// probe of the loop alone: three vector instructions 12.6, the matrix
+// instruction 9.4; they do not overlap, from one wave or from several), which
+// is three fifths of the kernel; the rest are the group's words, the staging
+// and the scan.  Two waves per SIMD hold the sums of eight planes (120
+// registers) without spills, so no wave waits on memory that it has not asked
+// for a step ahead: the bounds of the next 64 runs, the next chunk's positions
+// and weights and the next group's LDS words are in flight while the current
+// ones are used.  Against sub-blocks of 4^3 cells with a sum, a compare, a
+// select and two products per pair (half tiles, three waves per SIMD): 2M
+// trajectories on 128^3 cells 4.79 -> 3.75 ms (24.8 TFLOP/s of the 15 flops
+// per included pair), 32.8M on 256^3 279.6 -> 203 ms (39 TFLOP/s).
+template <int MODE, bool COUNT, int PLAN>
+__device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile)
+{
+    using L = PlaneLds;
+    constexpr int W = GatherWaves<3>::value, TE = Geo<3>::TE, ZP = TE, C = 4, NA = 5;
+    constexpr int NB = L::NB, HZ = ZP / 2, GR = kPlaneRecs;
+    constexpr bool kGeneral = MODE == kNwGeneral;
+    static_assert(GR * ZP == 16, "one row of lanes per group");
+    static_assert(sizeof(L) * W >= sizeof(double) * W * 4 * NA * kWave, "four planes of sums must fit");
+    __shared__ L lds[W];
+    __shared__ RunTable runs;
+    __shared__ double xcs[3][TE];
+
+    const MeshDev& m = g.m;
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    L& my = lds[wave];
+    int tc[3];
+    tc[0] = tile % m.nt[0];
+    tc[1] = (tile / m.nt[0]) % m.nt[1];
+    tc[2] = tile / (m.nt[0] * m.nt[1]);
+
+    if (threadIdx.x < 3 * TE) {
+        const int a = threadIdx.x / TE, p = threadIdx.x % TE;
+        const int64_t idx = (int64_t)tc[a] * TE + p;
+        xcs[a][p] = idx < m.n[a] ? (kGeneral ? cell_centre(m, a, idx) : uniform_centre(m, a, idx))
+                                 : __builtin_nan("");
+    }
+    if (threadIdx.x >= kWave && threadIdx.x < kWave + kClasses) {
+        const int k = threadIdx.x - kWave;
+        const uint32_t kb = (uint32_t)k * (uint32_t)m.ntiles;
+        int n = 0;
+        if (g.bstart[kb] != g.bstart[kb + m.ntiles]) {
+            ClassRows cr;
+            class_rows<3>(m, tc, k, cr);
+            n = cr.nrows * cr.nruns;
+            runs.cls[k] = cr;
+        }
+        int incl = n;
+#pragma unroll
+        for (int o = 1; o < kClasses; o <<= 1) {
+            const int t = __shfl_up(incl, o, kClasses);
+            if (k >= o) incl += t;
+        }
+        runs.base[k + 1] = incl;
+        if (k == 0) runs.base[0] = 0;
+    }
+    const int lx = lane & 7, ly = lane >> 3;
+    // Scaled squares: B = 2^bexp takes c^2 to about 2^64, so that differences
+    // of scaled sums are 0, negative or far above 1 (bexp is even: 2^(bexp/2)
+    // scales 1/h).  cmid: the real number below which (tie: up to which) a sum
+    // of two binary32 numbers rounds to at most c^2.
+    const float c2 = uniform_value((float)g.cutoff * (float)g.cutoff);
+    const int bexp = (64 - (c2 > 0.0f ? ilogbf(c2) : -150)) & ~1;
+    const float c2b = uniform_value(ldexpf(c2, bexp));
+    const bool tiny = bexp > 100;          // the factor below would be subnormal
+    const float ek = uniform_value(ldexpf(-0.72134752044448170368f, tiny ? 0 : -bexp));
+    // just below cmid where the tie rounds up, so that a sum equal to it fails
+    double cmid = ldexp(0.5 * ((double)c2 + (double)__int_as_float(__float_as_int(c2) + 1)), bexp);
+    if (__float_as_int(c2) & 1) cmid = __longlong_as_double(__double_as_longlong(cmid) - 1);
+    cmid = uniform_value(cmid);
+
+    __syncthreads();
+    double bmid[3], bhalf[3];
+    bool faxis[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        double f, l;
+        if (kGeneral && m.edges[a]) {
+            int p1 = TE - 1;
+            const int last = (int)(m.n[a] - 1 - (int64_t)tc[a] * TE);
+            if (p1 > last) p1 = last;
+            f = xcs[a][0];
+            l = xcs[a][p1];
+        } else {
+            const int64_t c0 = (int64_t)tc[a] * TE;
+            f = uniform_centre(m, a, c0);
+            l = uniform_centre(m, a, c0 + TE - 1);
+        }
+        bmid[a] = uniform_value(0.5 * (f + l));
+        bhalf[a] = uniform_value(0.5 * (l - f));
+        faxis[a] = !(m.periodic[a] && 4.0 * bhalf[a] >= m.L[a]);
+    }
+
+    F4 acc[ZP];
+    float den[ZP];
+    double tot[ZP][NA];
+    uint32_t cnt[ZP];
+#pragma unroll
+    for (int z = 0; z < ZP; ++z) {
+        acc[z] = F4{0.f, 0.f, 0.f, 0.f};
+        den[z] = 0.f;
+        cnt[z] = 0;
+#pragma unroll
+        for (int k = 0; k < NA; ++k) tot[z][k] = 0.0;
+    }
+    auto fold = [&]() {
+#pragma unroll
+        for (int z = 0; z < ZP; ++z) {
+            tot[z][0] += (double)den[z];
+            den[z] = 0.f;
+#pragma unroll
+            for (int k = 0; k < C; ++k) tot[z][1 + k] += (double)acc[z][k];
+            acc[z] = F4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    const uint64_t ltmask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+
+    // ---- one batch of n <= NB candidates of this wave.  Lanes e and e + 32
+    // stage record e: the lower half takes x and the first half of the planes,
+    // the upper half y and the others (12 positions each).
+    auto process = [&](int n) {
+        wave_sync();
+        const int e = lane & (NB - 1), half = lane / NB;
+        PlaneGroup& gp = my.grp[e / GR];
+        const int er = e % GR;
+        // least s B of the lane's 8 positions along x or y, largest threshold
+        // of its planes by twos
+        float smin = r_inf<float>(), thi[2] = {-3.0e38f, -3.0e38f};
+        if (e < n) {
+            const double4 P = my.pos[e];
+            const bool delta = MODE == FLA_DEPOSIT && P.w < 0.0;
+            const double hb = ldexp(delta ? -P.w : P.w, bexp / 2);
+            // np positions of axis a from position p0 on: s B and e
+            auto axis = [&](int a, double xa, int p0, double mid, double halfw, auto npc, float* sv, float* ev) {
+                constexpr int np = decltype(npc)::value;
+                double d[np];
+#pragma unroll
+                for (int q = 0; q < np; ++q) d[q] = xcs[a][p0 + q] - xa;
+                if (m.periodic[a]) {
+                    // the tile's box bounds the offsets
+                    const double dm = fabs(mid - xa) + halfw, La = m.L[a];
+                    if (dm > 0.5 * La) {
+                        if (dm < La) {
+#pragma unroll
+                            for (int q = 0; q < np; ++q) {
+#pragma clang fp contract(off)
+                                const double w = d[q] > 0.0 ? d[q] - La : d[q] + La;
+                                d[q] = fabs(d[q]) <= 0.5 * La ? d[q] : w;
+                            }
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < np; ++q) d[q] = min_image(d[q], La);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < np; ++q) {
+                    sv[q] = (float)scaled_sq(d[q], hb);
+                    ev[q] = __builtin_amdgcn_exp2f((tiny ? ldexpf(sv[q], -bexp) : sv[q]) * ek);
+                }
+                if (MODE == FLA_DEPOSIT && delta) {
+                    // whole amount into the home cell: factor 1 there, 0 elsewhere
+                    const int64_t hcell = home_index(m, a, xa);
+#pragma unroll
+                    for (int q = 0; q < np; ++q) {
+                        const bool home = (int64_t)tc[a] * TE + p0 + q == hcell;
+                        sv[q] = home ? 0.f : r_inf<float>();
+                        ev[q] = home ? 1.f : 0.f;
+                    }
+                }
+            };
+            float sv[TE], ev[TE];
+            axis(half, half ? P.y : P.x, 0, half ? bmid[1] : bmid[0], 1.001 * (half ? bhalf[1] : bhalf[0]),
+                 std::integral_constant<int, TE>{}, sv, ev);
+            float4* row = (float4*)(half ? gp.y[er] : gp.x[er]);
+#pragma unroll
+            for (int q = 0; q < TE; ++q) smin = fminf(smin, sv[q]);   // ignores NaN (a centre beyond the mesh)
+#pragma unroll
+            for (int q = 0; q < TE; q += 2) row[q / 2] = make_float4(sv[q], ev[q], sv[q + 1], ev[q + 1]);
+            axis(2, P.z, half * HZ, bmid[2], 1.001 * bhalf[2], std::integral_constant<int, HZ>{}, sv, ev);
+            const float4 wa = my.wa[e];
+            float tv[HZ];
+#pragma unroll
+            for (int q = 0; q < HZ; ++q) {
+                // the binary32 number after c^2 (middle) - s_z truncated: the
+                // least that s_x + s_y must stay below
+                const uint64_t r = __double_as_longlong(cmid - (double)sv[q]);
+                const uint32_t tr = __builtin_amdgcn_alignbit((uint32_t)(r >> 32) - (896u << 20), (uint32_t)r, 29);
+                tv[q] = sv[q] <= c2b ? __int_as_float((int)(tr + 1)) : -3.0e38f;
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) thi[q] = fmaxf(tv[2 * q], tv[2 * q + 1]);
+            float4* td = (float4*)&gp.td[er][half * HZ];
+            td[0] = make_float4(tv[0], wa.x * ev[0], tv[1], wa.x * ev[1]);
+            td[1] = make_float4(tv[2], wa.x * ev[2], tv[3], wa.x * ev[3]);
+            *(float4*)&gp.ez[er][half * HZ] = make_float4(ev[0], ev[1], ev[2], ev[3]);
+            if (half) *(float4*)gp.q[er] = make_float4(wa.y, wa.z, wa.w, my.wb[e]);
+        } else if (e < (n + GR - 1) / GR * GR) {
+            // slots that fill up the last group reach nothing
+            const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f), none = make_float4(-3.0e38f, 0.f, -3.0e38f, 0.f);
+            float4* row = (float4*)(half ? gp.y[er] : gp.x[er]);
+#pragma unroll
+            for (int q = 0; q < TE / 2; ++q) row[q] = zero;
+            float4* td = (float4*)&gp.td[er][half * HZ];
+            td[0] = none;
+            td[1] = none;
+            *(float4*)&gp.ez[er][half * HZ] = zero;
+            if (half) *(float4*)gp.q[er] = zero;
+        }
+        // records that reach planes 2 h and 2 h + 1 (sums of the least terms: no
+        // pair is missed), one bit each; lower lanes hold h = 0, 1, upper ones
+        // h = 2, 3
+        uint32_t reach[ZP / 2];
+        {
+            const auto mn = __builtin_amdgcn_permlane32_swap(__float_as_uint(smin), __float_as_uint(smin), false, false);
+            const float mxy = __uint_as_float(mn[0]) + __uint_as_float(mn[1]);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const uint64_t any = __ballot(mxy < thi[q]);
+                reach[q] = (uint32_t)any;
+                reach[q + 2] = (uint32_t)(any >> 32);
+            }
+        }
+        wave_sync();
+        // the next group's words are read while the current group is summed
+        struct Words {
+            float2 td, fx[GR], fy[GR];
+            float ez, q;
+        };
+        auto load = [&](const PlaneGroup& p, Words& w) {
+            w.td = (&p.td[0][0])[lane & 15];
+            w.ez = (&p.ez[0][0])[lane >> 2];
+            w.q = p.q[lane >> 5][lane & 3];
+#pragma unroll
+            for (int r = 0; r < GR; ++r) {
+                w.fx[r] = p.x[r][lx];
+                w.fy[r] = p.y[r][ly];
+            }
+        };
+        constexpr int UG = 4;              // groups per step of the loop
+        Words w, nx;
+        load(my.grp[0], nx);
+#pragma unroll 1
+        for (int g0 = 0; g0 * GR < n; g0 += UG) {
+            static_for<0, UG>([&](auto gc) {
+                constexpr int u = decltype(gc)::value;
+                w = nx;
+                load(my.grp[g0 + u + 1], nx);   // past the last group: words that are not used
+                const float tz = w.td.x, dz = w.td.y, aw = w.ez * w.q;
+                float sxy[GR], exy[GR];
+#pragma unroll
+                for (int r = 0; r < GR; ++r) {
+                    sxy[r] = w.fx[r].x + w.fy[r].x;
+                    exy[r] = w.fx[r].y * w.fy[r].y;
+                }
+                // both records in planes z and z + 1
+                auto planes2 = [&](auto zc) {
+                    constexpr int z = decltype(zc)::value, j = ZP + z;
+                    float a0 = row_bcast<z>(tz) - sxy[0], b0 = row_bcast<z + 1>(tz) - sxy[0];
+                    float a1 = row_bcast<j>(tz) - sxy[1], b1 = row_bcast<j + 1>(tz) - sxy[1];
+                    if (COUNT) {
+                        cnt[z] += (a0 > 0.f ? 1u : 0u) + (a1 > 0.f ? 1u : 0u);
+                        cnt[z + 1] += (b0 > 0.f ? 1u : 0u) + (b1 > 0.f ? 1u : 0u);
+                    }
+                    weigh2<z, z + 1>(a0, b0, exy[0], dz, den[z], den[z + 1]);
+                    weigh2<j, j + 1>(a1, b1, exy[1], dz, den[z], den[z + 1]);
+                    // the matrix instructions stay together: each costs about
+                    // three times its 8 cycles between vector instructions
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[z] = __builtin_amdgcn_mfma_f32_4x4x1f32(aw, a0, acc[z], 4, z, 0);
+                    acc[z + 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(aw, b0, acc[z + 1], 4, z + 1, 0);
+                    acc[z] = __builtin_amdgcn_mfma_f32_4x4x1f32(aw, a1, acc[z], 4, j, 0);
+                    acc[z + 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(aw, b1, acc[z + 1], 4, j + 1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                // PLAN: granularity of the skips (a skipped pair only saves
+                // additions of zero): 1 two planes, 2 four, 3 all
+                constexpr int S = PLAN == 1 ? 2 : PLAN == 2 ? 4 : ZP;
+                static_for<0, ZP / S>([&](auto hc) {
+                    constexpr int h = decltype(hc)::value;
+                    uint32_t any = 0;
+#pragma unroll
+                    for (int v = 0; v < S / 2; ++v) any |= reach[h * (S / 2) + v];
+                    if (any & (((1u << GR) - 1) << (GR * u)))
+                        static_for<0, S / 2>([&](auto zc) {
+                            planes2(std::integral_constant<int, S * h + 2 * decltype(zc)::value>{});
+                        });
+                });
+            });
+#pragma unroll
+            for (int h = 0; h < ZP / 2; ++h) reach[h] >>= GR * UG;
+        }
+        wave_sync();
+    };
+
+    // ---- scan.  Lane l holds run l of the current 64 runs: records s0 to s1
+    // and its first chunk; chunk c, c + W, ... are this wave's.
+    const int nrun = runs.base[kClasses];
+    auto run_of = [&](int f, uint32_t& a0, uint32_t& a1) {
+        a0 = a1 = 0;
+        if (f >= nrun) return;
+        int k = 0;
+        while (runs.base[k + 1] <= f) ++k;
+        const ClassRows& cr = runs.cls[k];
+        const int j = f - runs.base[k];
+        const int q = cr.nruns == 2 ? j & 1 : 0;
+        const uint32_t rb = row_bucket<3>(m, cr, cr.nruns == 2 ? j >> 1 : j);
+        a0 = g.bstart[rb + cr.runs[q][0]];
+        a1 = g.bstart[rb + cr.runs[q][1] + 1];
+    };
+    uint32_t s0 = 0, s1 = 0, first = 0, s0n, s1n;
+    int f0 = 0;
+    uint32_t c = (uint32_t)wave, nchunk = 0;
+    run_of(lane, s0n, s1n);
+    double4 Pn = make_double4(0, 0, 0, 0);
+    float4 wan = make_float4(0, 0, 0, 0);
+    float wbn = 0.f;
+    bool okn = false;
+    int ncand = 0, nfold = 0;
+    for (bool more = true; more;) {
+        const double4 P = Pn;
+        const float4 wa = wan;
+        const float wb = wbn;
+        const bool inr = okn;
+        // the next chunk, if there is one
+        okn = false;
+        while (c >= nchunk) {
+            c -= nchunk;
+            nchunk = 0;
+            if (f0 >= nrun) {
+                more = false;
+                break;
+            }
+            s0 = s0n;
+            s1 = s1n;
+            f0 += kWave;
+            run_of(f0 + lane, s0n, s1n);
+            const uint32_t nc = (s1 - s0 + kWave - 1) / kWave;
+            uint32_t incl = nc;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const uint32_t t = __shfl_up(incl, o, kWave);
+                if (lane >= o) incl += t;
+            }
+            first = incl - nc;
+            nchunk = __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        if (more) {
+            const int j = __popcll(__ballot(first <= c)) - 1;
+            const uint32_t p = __builtin_amdgcn_readlane(s0, j) + (c - __builtin_amdgcn_readlane(first, j)) * kWave + lane;
+            okn = p < __builtin_amdgcn_readlane(s1, j);
+            c += W;
+            if (okn) {
+                Pn = g.rpos[p];
+                const float* w = (const float*)g.rw + (size_t)p * kRecW;
+                wan = *(const float4*)w;
+                wbn = w[4];
+            }
+        }
+        const bool ok = inr && near_tile<MODE == FLA_DEPOSIT>(m, P, tc, bmid, bhalf, faxis, g.filt2);
+        const uint64_t bal = __ballot(ok);
+        if (ok) {
+            const int at = ncand + __popcll(bal & ltmask);
+            my.pos[at] = P;
+            my.wa[at] = wa;
+            my.wb[at] = wb;
+        }
+        ncand += __popcll(bal);
+        while (ncand >= (more ? NB : 1)) {
+            const int n = ncand < NB ? ncand : NB;
+            process(n);
+            // binary32 partial sums run over at most 64 records
+            if (++nfold == kWave / NB) {
+                fold();
+                nfold = 0;
+            }
+            const int rem = ncand - n;
+            if (rem > 0) {
+                const int at = n + (lane < rem ? lane : 0);
+                const double4 mp = my.pos[at];
+                const float4 ma = my.wa[at];
+                const float mb = my.wb[at];
+                wave_sync();
+                if (lane < rem) {
+                    my.pos[lane] = mp;
+                    my.wa[lane] = ma;
+                    my.wb[lane] = mb;
+                }
+            }
+            ncand = rem;
+        }
+    }
+    fold();
+
+    // ---- the waves' sums, four planes at a time through LDS, added in wave
+    // order; then divide (NW) or scale by 1/V_c (deposition), sign, scale
+    double* red = reinterpret_cast<double*>(lds);   // [wave][plane][k][lane]
+    const int64_t cx = (int64_t)tc[0] * TE + lx, cy = (int64_t)tc[1] * TE + ly;
+    const bool in_xy = cx < m.n[0] && cy < m.n[1];
+#pragma unroll
+    for (int z0 = 0; z0 < ZP; z0 += 4) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < NA; ++k) red[((wave * 4 + u) * NA + k) * kWave + lane] = tot[z0 + u][k];
+        __syncthreads();
+        const int64_t cz = (int64_t)tc[2] * TE + z0 + wave;
+        if (in_xy && cz < m.n[2]) {
+            const int64_t lin = cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * cz);
+            double sum[NA];
+#pragma unroll
+            for (int k = 0; k < NA; ++k) {
+                double a = 0.0;
+#pragma unroll
+                for (int v = 0; v < W; ++v) a += red[((v * 4 + wave) * NA + k) * kWave + lane];
+                sum[k] = a;
+            }
+            const double f = -g.scale * (g.cell_scale ? (double)((const float*)g.cell_scale)[lin] : 1.0);
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const double val = MODE != FLA_DEPOSIT ? (sum[0] > 0.0 ? f * (sum[1 + k] / sum[0]) : 0.0)
+                                                       : f * sum[1 + k] / m.vol;
+                ((float*)g.out[k])[lin] = (float)val;
+            }
+            if (g.den) ((float*)g.den)[lin] = (float)sum[0];
+        }
+    }
+    if (COUNT) {
+        // every wave holds counts for all of the workgroup's cells; integer
+        // sums do not depend on the order of the atomic additions
+        unsigned long long npairs = 0;
+#pragma unroll
+        for (int z = 0; z < ZP; ++z) {
+            npairs += cnt[z];
+            const int64_t cz = (int64_t)tc[2] * TE + z;
+            if (g.pairs && cnt[z] && in_xy && cz < m.n[2])
+                atomicAdd(&g.pairs[cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * cz)], cnt[z]);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) npairs += __shfl_xor(npairs, o, kWave);
+        if (lane == 0 && npairs) atomicAdd(&g.stats[ST_PAIRS], npairs);
+    }
+}
+
 // The work of one workgroup: every cell of its part `work % TP` of tile
 // `work / TP` of the mesh of g.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
@@ -495,9 +1052,6 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
         // every lane keeps the mask of one staged record (read with readlane,
         // no LDS round trip)
         const int maskv = (lane < n) ? my.mask[lane] : 0;
-        // union of the masks of records 4q .. 4q + 3, on the lanes of quad q
-        int mask4 = maskv | __builtin_amdgcn_mov_dpp(maskv, 0xB1, 0xF, 0xF, false);
-        mask4 = mask4 | __builtin_amdgcn_mov_dpp(mask4, 0x4E, 0xF, 0xF, false);
         // one sub-block of one record: the per-pair inclusion test, then the
         // denominator multiply-add and the C channel multiply-adds.  In
         // binary32 the channels go to one v_mfma_f32_4x4x1_16b_f32: with A
@@ -507,7 +1061,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
         // so that register k of lane l accumulates channel k of the lane's
         // cell: the layout of the vector path, with 4 multiply-adds per lane
         // moved off the vector unit.
-        auto sub = [&](int b, const R4* t, const R2& ts, const R* wv, float wq, bool live = true) {
+        auto sub = [&](int b, const R4* t, const R2& ts, const R* wv, float wq) {
             R s, ew;
             if constexpr (TP == 2) {
                 // x split: ts holds the owned half of x, t the y and z tables
@@ -534,27 +1088,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
 #pragma unroll
                 for (int k = 0; k < NA; ++k) part[b][k] = fma(ew, wv[k], part[b][k]);
             }
-            if (COUNT) cntb[b] += (in && live) ? 1u : 0u;
-        };
-        // x split, sub-block b = by + 2 bz: the pair (by, 0), (by, 1) shares
-        // s_x + s_y and e_x e_y
-        auto pre = [&](int by, const R4* t, const R2& ts, R& sxy, R& exy) {
-            sxy = ts.x + (by ? t[0].z : t[0].x);
-            exy = ts.y * (by ? t[0].w : t[0].y);
-        };
-        auto fin = [&](int b, int bz, R sxy, R exy, const R4* t, const R* wv, float wq, bool live) {
-            const R s = sxy + (bz ? t[1].z : t[1].x);
-            R ew = exy * (bz ? t[1].w : t[1].y);
-            const bool in = s <= c2;
-            ew = in ? ew : (R)0;
-            if constexpr (kMfma) {
-                part[b][0] = fma(ew, wv[0], part[b][0]);
-                acc[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(wq, (float)ew, acc[b], 4, 0, 0);
-            } else {
-#pragma unroll
-                for (int k = 0; k < NA; ++k) part[b][k] = fma(ew, wv[k], part[b][k]);
-            }
-            if (COUNT) cntb[b] += (in && live) ? 1u : 0u;
+            if (COUNT) cntb[b] += in ? 1u : 0u;
         };
         // PLAN sets the granularity of the wave-uniform skips of a record that
         // reaches the workgroup's part: 0 one branch per sub-block, 1 per
@@ -613,88 +1147,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
         R2 hA, hB;
         R wA[NA], wB[NA];
         float qA, qB;
-        if (PLAN == 1 && D == 3 && kMfma) {
-            // Four records per step.  A pair of sub-blocks is evaluated for
-            // all four records when any of them reaches it: a record that
-            // reaches no cell there adds exact zeros (its kernel weights are
-            // 0 on every lane), so the sums are those of one record at a
-            // time, while the tests and branches are shared by four records
-            // and the four independent chains fill the issue slots.  Slots
-            // past the batch end repeat record e with zero weights and are
-            // not counted as pairs.
-            R4 tC[NT], tD[NT];
-            R2 hC, hD;
-            R wC[NA], wD[NA];
-            float qC, qD;
-            for (int e = 0; e < n; e += 4) {
-                const bool l1 = e + 1 < n, l2 = e + 2 < n, l3 = e + 3 < n;
-                const int e1 = l1 ? e + 1 : e;
-                const int e2 = l2 ? e + 2 : e;
-                const int e3 = l3 ? e + 3 : e;
-                load_t(e, tA, hA);
-                load_t(e1, tB, hB);
-                load_t(e2, tC, hC);
-                load_t(e3, tD, hD);
-                load_w(e, wA, qA);
-                load_w(e1, wB, qB);
-                load_w(e2, wC, qC);
-                load_w(e3, wD, qD);
-                if (!l1) {
-#pragma unroll
-                    for (int k = 0; k < NA; ++k) wB[k] = 0;
-                    qB = 0.0f;
-                }
-                if (!l2) {
-#pragma unroll
-                    for (int k = 0; k < NA; ++k) wC[k] = 0;
-                    qC = 0.0f;
-                }
-                if (!l3) {
-#pragma unroll
-                    for (int k = 0; k < NA; ++k) wD[k] = 0;
-                    qD = 0.0f;
-                }
-                const int mk = __builtin_amdgcn_readlane(mask4, e);
-                if (mk == 0) continue;
-                if constexpr (TP == 2) {
-#pragma unroll
-                    for (int q = 0; q < NSB / 2; ++q) {
-                        const bool m0 = (mk >> q) & 1, m1 = (mk >> (q + NSB / 2)) & 1;
-                        if (!(m0 || m1)) continue;
-                        R sxy[4], exy[4];
-                        pre(q, tA, hA, sxy[0], exy[0]);
-                        pre(q, tB, hB, sxy[1], exy[1]);
-                        pre(q, tC, hC, sxy[2], exy[2]);
-                        pre(q, tD, hD, sxy[3], exy[3]);
-                        if (m0) {
-                            fin(q, 0, sxy[0], exy[0], tA, wA, qA, true);
-                            fin(q, 0, sxy[1], exy[1], tB, wB, qB, l1);
-                            fin(q, 0, sxy[2], exy[2], tC, wC, qC, l2);
-                            fin(q, 0, sxy[3], exy[3], tD, wD, qD, l3);
-                        }
-                        if (m1) {
-                            fin(q + NSB / 2, 1, sxy[0], exy[0], tA, wA, qA, true);
-                            fin(q + NSB / 2, 1, sxy[1], exy[1], tB, wB, qB, l1);
-                            fin(q + NSB / 2, 1, sxy[2], exy[2], tC, wC, qC, l2);
-                            fin(q + NSB / 2, 1, sxy[3], exy[3], tD, wD, qD, l3);
-                        }
-                    }
-                    continue;
-                }
-#pragma unroll
-                for (int q = 0; q < NSB / 2; ++q)
-                    if (mk & (((1 << (NSB / 2)) | 1) << q)) {
-                        sub(q, tA, hA, wA, qA);
-                        sub(q + NSB / 2, tA, hA, wA, qA);
-                        sub(q, tB, hB, wB, qB, l1);
-                        sub(q + NSB / 2, tB, hB, wB, qB, l1);
-                        sub(q, tC, hC, wC, qC, l2);
-                        sub(q + NSB / 2, tC, hC, wC, qC, l2);
-                        sub(q, tD, hD, wD, qD, l3);
-                        sub(q + NSB / 2, tD, hD, wD, qD, l3);
-                    }
-            }
-        } else {
+        {
             // one record at a time; the factors of the next record are read
             // while the current one is accumulated
             load_t(0, tA, hA);
@@ -830,23 +1283,26 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
     }
 }
 
+// Work item `work` by the body of its precision and dimension.
+template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
+__device__ __forceinline__ void gather_work(const GatherArgs& g, const int work)
+{
+    if constexpr (sizeof(R) == 4 && D == 3)
+        gather_planes<MODE, COUNT, PLAN>(g, work);
+    else
+        gather_tile<R, D, MODE, COUNT, PLAN, TP>(g, work);
+}
+
 // Slot b of the launch belongs to XCD b % kXcds and computes the work item
-// order[xcd_remap(b)] (the heaviest items of each XCD first).  Without a
-// queue every workgroup takes its own slot; with one, the workgroups (as many
-// as the compute units hold) take their XCD's slots x, x + kXcds, ... in
-// order from that XCD's counter until they pass the end, so a workgroup that
-// finishes early starts the next item at once (128^3: 4.93 -> 4.80 ms).  Which
-// workgroup computes an item does not change its results.
+// order[xcd_remap(b)] (the heaviest items of each XCD first).  The workgroups
+// (as many as the compute units hold) take their XCD's slots x, x + kXcds,
+// ... in order from that XCD's counter until they pass the end, so a
+// workgroup that finishes early starts the next item at once (128^3: 4.93 ->
+// 4.80 ms).  Which workgroup computes an item does not change its results.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
 static __global__ __launch_bounds__(kWave * GatherWaves<D>::value, (GatherOcc<R, D, TP>::value)) void k_gather(GatherArgs g)
 {
     const int total = g.m.ntiles * TP;
-    if (!g.queue) {
-        int w = xcd_remap(blockIdx.x, total);
-        if (g.order) w = g.order[w];
-        gather_tile<R, D, MODE, COUNT, PLAN, TP>(g, w);
-        return;
-    }
     __shared__ int s_slot;
     const int x = blockIdx.x % kXcds;
     for (;;) {
@@ -856,8 +1312,8 @@ static __global__ __launch_bounds__(kWave * GatherWaves<D>::value, (GatherOcc<R,
         const int slot = s_slot;
         if (slot >= total) break;
         int w = xcd_remap(slot, total);
-        if (g.order) w = g.order[w];
-        gather_tile<R, D, MODE, COUNT, PLAN, TP>(g, w);
+        w = g.order[w];
+        gather_work<R, D, MODE, COUNT, PLAN, TP>(g, w);
     }
 }
 
@@ -978,18 +1434,23 @@ static __global__ __launch_bounds__(kWave * GatherWaves<D>::value, (GatherOcc<R,
             else
                 hi = mid - 1;
         }
-        gather_tile<R, D, MODE, COUNT, PLAN, TP>(items[lo].g, (j - items[lo].tile_base) * TP + u % TP);
+        gather_work<R, D, MODE, COUNT, PLAN, TP>(items[lo].g, (j - items[lo].tile_base) * TP + u % TP);
     }
 }
+
+// Plan 0 of binary32 in 3-D is plan 1: two planes of two records are the
+// finest unit of its skips.
+template <typename R, int D> constexpr int finest_plan() { return sizeof(R) == 4 && D == 3 ? 1 : 0; }
 
 template <typename R, int D, int MODE, bool COUNT, int TP>
 static void launch_plan(const GatherArgs& g, int plan, dim3 grid, dim3 block, hipStream_t s)
 {
+    constexpr int kFinest = finest_plan<R, D>();
     switch (plan) {
     case 1: FLA_LAUNCH((k_gather<R, D, MODE, COUNT, 1, TP>), grid, block, 0, s, g); break;
     case 2: FLA_LAUNCH((k_gather<R, D, MODE, COUNT, 2, TP>), grid, block, 0, s, g); break;
     case 3: FLA_LAUNCH((k_gather<R, D, MODE, COUNT, 3, TP>), grid, block, 0, s, g); break;
-    default: FLA_LAUNCH((k_gather<R, D, MODE, COUNT, 0, TP>), grid, block, 0, s, g); break;
+    default: FLA_LAUNCH((k_gather<R, D, MODE, COUNT, kFinest, TP>), grid, block, 0, s, g); break;
     }
 }
 
@@ -1011,11 +1472,12 @@ static void launch_batch_plan(const BatchItem* items, int nsnap, int nwork, int 
     if (nb > total) nb = total;
     if (nb < 1) nb = 1;
     dim3 grid((unsigned)nb), block(kWave * GatherWaves<D>::value);
+    constexpr int kFinest = finest_plan<R, D>();
     switch (plan) {
     case 1: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 1, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
     case 2: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 2, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
     case 3: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 3, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
-    default: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 0, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
+    default: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, kFinest, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
     }
 }
 
@@ -1046,8 +1508,8 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
     // the XCD counters start at zero (a fill kernel: the launch may be captured)
     hipError_t e = launch_fill_u32(queue, kXcds, 0u, s);
     if (e != hipSuccess) return e;
-    if constexpr (D == 3) {
-        if (tile_parts(D, shape) == 2) {
+    if constexpr (tile_parts<R>(D, 0) == 2) {
+        if (tile_parts<R>(D, shape) == 2) {
             launch_batch_shape<R, D, 2>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu, s);
             return hipGetLastError();
         }
@@ -1059,20 +1521,15 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
 template <typename R, int D, int TP>
 static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, hipStream_t s)
 {
-    if (g.order) {
-        FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
-        FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP,
-                   g.order);
-    }
+    FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
+    FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP, g.order);
+    // as many workgroups as the compute units hold at once; the XCD
+    // counters start at zero (a fill kernel: the launch may be captured)
     int64_t nb = (int64_t)g.m.ntiles * TP;
-    if (g.queue) {
-        // as many workgroups as the compute units hold at once; the XCD
-        // counters start at zero (a fill kernel: the launch may be captured)
-        const int64_t fit = resident_workgroups<R, D, TP>(g.ncu);
-        if (fit < nb) nb = fit;
-        hipError_t e = launch_fill_u32(g.queue, kXcds, 0u, s);
-        if (e != hipSuccess) return e;
-    }
+    const int64_t fit = resident_workgroups<R, D, TP>(g.ncu);
+    if (fit < nb) nb = fit;
+    hipError_t e = launch_fill_u32(g.queue, kXcds, 0u, s);
+    if (e != hipSuccess) return e;
     dim3 grid((unsigned)nb), block(kWave * GatherWaves<D>::value);
     const bool general = g.m.edges[0] || g.m.edges[1] || g.m.edges[2];
     if (mode == FLA_NW && general) {
@@ -1099,8 +1556,8 @@ hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_cod
 {
     if (g.m.ntiles <= 0) return hipSuccess;
     const int plan = plan_code % kGatherPlans, shape = plan_code / kGatherPlans;
-    if constexpr (D == 3) {
-        if (tile_parts(D, shape) == 2) return launch_gather_shape<R, D, 2>(g, mode, count, plan, s);
+    if constexpr (tile_parts<R>(D, 0) == 2) {
+        if (tile_parts<R>(D, shape) == 2) return launch_gather_shape<R, D, 2>(g, mode, count, plan, s);
     }
     return launch_gather_shape<R, D, 1>(g, mode, count, plan, s);
 }

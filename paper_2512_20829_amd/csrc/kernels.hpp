@@ -19,12 +19,12 @@ struct GatherArgs {
     void* den;
     uint32_t* pairs;            // nullable per-cell included-pair counts (zeroed by the caller)
     unsigned long long* stats;
-    // optional (both set or both null): workspace for the work order of the
-    // single-snapshot gather, ntiles cost words and 2 * ntiles slot entries
+    // workspace for the work order of the single-snapshot gather, ntiles cost
+    // words and 2 * ntiles slot entries
     uint32_t* tile_cost;
     int* order;
-    // optional: kXcds counters of workspace for a persistent launch of ncu
-    // compute units' worth of workgroups (null: one workgroup per work item)
+    // kXcds counters of workspace for the persistent launch of ncu compute
+    // units' worth of workgroups
     uint32_t* queue;
     int ncu;
 };
@@ -102,8 +102,8 @@ hipError_t launch_deposit_norm(const MeshDev& m, const PhysDev& ph, const uint32
                                unsigned long long* stats, hipStream_t s);
 
 // Gather plan codes: plan + kGatherPlans * shape.  The plan sets how finely
-// the gather skips unreachable sub-blocks; the shape the part of a tile one
-// workgroup owns (0: half a tile along x in 3-D, the whole tile in 2-D;
+// the gather skips unreachable cells; the shape the part of a tile one
+// workgroup owns (0: half a tile along x in binary64 3-D, else the whole tile;
 // 1: the whole tile, 3-D only).
 constexpr int kGatherPlans = 4;
 constexpr int kGatherShapes = 2;
