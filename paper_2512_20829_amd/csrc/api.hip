@@ -2124,11 +2124,11 @@ fla_status cell_index_build(fla_ctx* ctx, const fla_cells* c, int32_t per_bucket
     layout(cv);
     HIP_OK(launch_cells_key(g, M, xc, keys, vals, s));
     bool in_alt = false;
-    HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, M, bits_for((uint64_t)nbk), rh, hist_w, scan, scan_w, s,
-                            &in_alt));
+    HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, M, bits_for((uint64_t)nbk << kCellsSubBits), rh, hist_w, scan,
+                            scan_w, s, &in_alt));
     const uint32_t* skeys = in_alt ? keys2 : keys;
     const uint32_t* svals = in_alt ? vals2 : vals;
-    HIP_OK(launch_bucket_bounds(skeys, M, (uint32_t)nbk, cstart, s));
+    HIP_OK(launch_bucket_bounds(skeys, M, (uint32_t)nbk, cstart, s, kCellsSubBits));
     for (int a = 0; a < D; ++a) HIP_OK(dev_malloc(ctx, (void**)&ix->xs[a], sizeof(double) * M));
     if (c->volume) HIP_OK(dev_malloc(ctx, (void**)&ix->vs, sizeof(double) * M));
     HIP_OK(dev_malloc(ctx, (void**)&ix->perm, sizeof(uint32_t) * M));

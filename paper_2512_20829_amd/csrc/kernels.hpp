@@ -88,8 +88,10 @@ hipError_t launch_prepass(const TrajDev& t, const MeshDev& m, const PhysDev& ph,
                           int deposit, uint32_t* keys, uint32_t* vals, double4* rpos, R* rw,
                           double* qd, unsigned long long* stats, hipStream_t s);
 
-hipError_t launch_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, uint32_t* bstart,
-                                hipStream_t s);
+// First position of every bucket b in [0, nb] in the sorted keys, whose bucket
+// is key >> shift.
+hipError_t launch_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, uint32_t* bstart, hipStream_t s,
+                                int shift = 0);
 hipError_t launch_max_class(const uint32_t* bstart, int ntiles, unsigned long long* stats, hipStream_t s);
 
 template <typename R>
@@ -193,6 +195,8 @@ hipError_t launch_cic(const PsiArgs& a, hipStream_t s);
 constexpr int kCellsMaxBuckets = 1024;   // per axis
 constexpr int kCellsHistBins = 65536;    // per axis, for the quantile edges
 constexpr int kCellsPerLane = 2;         // cells owned by each lane of the gather
+constexpr int kCellsSubBits = 3;         // low bits of a cell's sort key: its place in the bucket
+static_assert((1 << kCellsSubBits) <= kClasses, "a bucket index and its low bits share 31 bits");
 constexpr int kCellsPerItem = kWave * kCellsPerLane;
 
 struct CellGridDev {

@@ -106,16 +106,16 @@ __global__ void k_max_class_batch(const BatchItem* items, int nsnap, const uint3
     if (threadIdx.x == 0) stats[ST_MAXCLASS] = mc;
 }
 
-// Bucket starts from sorted keys: bstart[b] = first position with key >= b
+// Bucket starts from sorted keys: bstart[b] = first position with bucket >= b
 // (binary search), one thread per bucket b in [0, nb].
-__global__ void k_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, uint32_t* bstart)
+__global__ void k_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, uint32_t* bstart, int shift)
 {
     int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b > (int64_t)nb) return;
     int64_t lo = 0, hi = n;
     while (lo < hi) {
         int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)keys[mid] < b)
+        if ((int64_t)(keys[mid] >> shift) < b)
             lo = mid + 1;
         else
             hi = mid;
@@ -346,11 +346,11 @@ hipError_t launch_prepass(const TrajDev& t, const MeshDev& m, const PhysDev& ph,
     return hipGetLastError();
 }
 
-hipError_t launch_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, uint32_t* bstart,
-                                hipStream_t s)
+hipError_t launch_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, uint32_t* bstart, hipStream_t s,
+                                int shift)
 {
     unsigned g = (unsigned)(((int64_t)nb + 1 + 255) / 256);
-    FLA_LAUNCH(k_bucket_bounds, dim3(g), dim3(256), 0, s, keys, n, nb, bstart);
+    FLA_LAUNCH(k_bucket_bounds, dim3(g), dim3(256), 0, s, keys, n, nb, bstart, shift);
     return hipGetLastError();
 }
 
