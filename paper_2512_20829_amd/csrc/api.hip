@@ -821,6 +821,11 @@ fla_status cic_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, double wei
     a.cptlog = a.ptlog[0] + a.ptlog[1] + a.ptlog[2];
     a.nblocks = kPsiBlocks;
     a.direct = sorted ? 1 : 0;
+    // workgroups of the reduction: what the compute units hold at once of its
+    // LDS sums, and no more than give each a thousand records
+    int ncu = 0;
+    HIP_OK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    a.nsplit = (int)std::min<int64_t>((int64_t)ncu * (sorted ? 1 : 2), std::max<int64_t>((t.count + 1023) / 1024, 1));
     const int64_t N = t.count;
     const int64_t hw = (int64_t)a.pntiles * a.nblocks + 1;
     const int64_t sw = scan_tmp_words(hw);

@@ -138,7 +138,7 @@ struct PsiArgs {
     int pnbins;                  // bins of 2^binlog consecutive tiles
     int binlog;                  // log2 tiles per bin: kPsiTilesPerBinLog, or 0 when direct
     int direct;                  // the scatter writes the tile buckets itself (bins are tiles; no tile pass)
-    int nsplit;                  // workgroups per bin in the tile pass
+    int nsplit;                  // workgroups per bin in the tile pass; of the whole CIC reduction
     unsigned int* binhist;       // pnbins * nblocks + 1, scanned in place
     unsigned int* tcursor;       // pntiles: next free slot of each tile bucket
     void* binned;                // records grouped by bin (loc = code, top bit = skip)
@@ -172,7 +172,7 @@ hipError_t launch_psicell(const PsiArgs& a, hipStream_t s);
 
 // One bucketed CIC particle: source terms, the fractional offsets from the
 // lower-corner cell centre along each axis, and that cell in its tile.
-template <typename R> struct CicRec {
+template <typename R> struct alignas(16) CicRec {
     R phi[4];
     R frac[3];
     uint32_t loc;

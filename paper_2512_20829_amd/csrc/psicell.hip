@@ -43,6 +43,8 @@
 // kPsiUnrollReduce) and issues all their loads before any use, to keep
 // enough reads in flight; the scatter forms the binary32 source terms of
 // binary32 records in binary32.
+#include <type_traits>
+
 #include "internal.hpp"
 #include "kernels.hpp"
 
@@ -56,8 +58,12 @@ constexpr int kPsiUnrollReduce = 8;    // reduce
 // cache lines (with 512 direct tiles, rounds of 2048, 4096 and 6144
 // binary32 records took the 200M-particle call to 6.72, 6.36 and 6.25 ms)
 template <typename R> struct PsiRoundPerThread { static constexpr int value = sizeof(R) == 4 ? 24 : 12; };
-// threads of a scatter block (a round is kPsiScatterThreads * U records)
-constexpr int kPsiScatterThreads = 256;
+// threads of a scatter block (a round is kPsiScatterThreads * U records).  A
+// round's particles are loaded while the one before is sorted and written,
+// which takes half of the registers of 8 waves: with nothing in flight then, the
+// 200M-particle scatter took 3.30 ms instead of 2.9 to 3.1 (the bytes it moves
+// take 2.2 at the rate of a copy), the CIC scatter of 50M 1.39 instead of 1.02
+constexpr int kPsiScatterThreads = 512;
 constexpr uint32_t kPsiSkip = 0xFFFFFFFFu;     // cell of a skipped record in a tile bucket
 constexpr uint32_t kPsiSkipBit = 0x80000000u;  // skip mark of a binned record (codes < 2^24)
 static_assert(kPsiTilesPerBin == kWave, "the tile pass scans one tile per lane of one wave");
@@ -251,27 +257,28 @@ __global__ __launch_bounds__(kPsiScatterThreads) void k_psi_scatter(PsiArgs a)
 #pragma unroll
     for (int k = 0; k < C; ++k) mx[k] = 0.0;
     unsigned long long bad = 0;
-    for (int64_t r0 = beg; r0 < end; r0 += RB) {
-        int code[U];
-        R v[U][3], ug[U][3], r[U];
+    int nxt[U];
+    R v[U][3], ug[U][3], r[U];
+    auto load = [&](int64_t r0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t p = r0 + (int64_t)u * NT + tid;
-            code[u] = p < end ? a.codes[p] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t p = r0 + (int64_t)u * NT + tid;
-            const bool live = code[u] >= 0;
+            const int64_t q = r0 + (int64_t)u * NT + tid, p = q < end ? q : end - 1;
+            nxt[u] = a.codes[p];
 #pragma unroll
             for (int ax = 0; ax < D; ++ax) {
-                v[u][ax] = live ? ((const R*)a.p.v[ax])[p] : (R)0;
-                ug[u][ax] = live ? ((const R*)a.p.ug[ax])[p] : (R)0;
+                v[u][ax] = ((const R*)a.p.v[ax])[p];
+                ug[u][ax] = ((const R*)a.p.ug[ax])[p];
             }
-            r[u] = live ? ((const R*)a.p.r)[p] : (R)1;
+            r[u] = ((const R*)a.p.r)[p];
         }
+    };
+    if (beg < end) load(beg);
+    for (int64_t r0 = beg; r0 < end; r0 += RB) {
+        int code[U];
         PsiRec<R> rec[U];
         unsigned int rank[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) code[u] = r0 + (int64_t)u * NT + tid < end ? nxt[u] : -1;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             rank[u] = 0;
@@ -296,6 +303,8 @@ __global__ __launch_bounds__(kPsiScatterThreads) void k_psi_scatter(PsiArgs a)
             for (int k = 0; k < C; ++k) mx[k] = fmax(mx[k], fabs((double)rec[u].phi[k]));
             rank[u] = atomicAdd(&cnt[code[u] >> bsh], 1u);
         }
+        // the next round's particles are read while this one is sorted and written
+        if (r0 + RB < end) load(r0 + RB);
         __syncthreads();
         // bins BPT tid .. BPT tid + BPT - 1
         const int b0 = BPT * tid;
@@ -478,11 +487,28 @@ __global__ void k_psi_scale(PsiArgs a)
     }
 }
 
+// Integer of |v| < 2^62 (binary64, from a product p w); with BIG, of a sum over
+// kPsiBigCount or more particles, |v| < 2^50 and adding 1.5 2^52 leaves the nearest integer in the low bits:
+// one fused multiply-add and a subtraction instead of a conversion to int64.
+constexpr int64_t kPsiBigCount = 4096;
+template <bool BIG>
+__device__ inline long long quantise(double p, double w, double& hi)
+{
+    if (BIG) {
+        constexpr double magic = 6755399441055744.0;      // 1.5 2^52
+        const double t = fma(p, w, magic);
+        hi = t - magic;
+        return __double_as_longlong(t) - 0x4338000000000000ll;
+    }
+    hi = rint(p * w);
+    return (long long)hi;
+}
+
 // One workgroup per tile: exact integer sums in LDS, then the tile's cells.
 // Records come from the tile pass (cell in tile, or kPsiSkip) or straight
 // from the scatter (the whole code, with the skip bit); both carry the cell
 // in the low bits and the skip bit set when skipped.
-template <typename R, int D, int NT>
+template <typename R, int D, int NT, bool BIG>
 __global__ __launch_bounds__(NT) void k_psi_reduce(PsiArgs a)
 {
     constexpr int C = D + 1;
@@ -509,21 +535,20 @@ __global__ __launch_bounds__(NT) void k_psi_reduce(PsiArgs a)
 #pragma unroll
         for (int u = 0; u < kPsiUnrollReduce; ++u) {
             const int64_t sl = s0 + (int64_t)u * blockDim.x;
-            if (sl < end) rec[u] = bucket[sl];
-            else rec[u].loc = kPsiSkip;
+            rec[u] = bucket[sl < end ? sl : end - 1];   // no branch between the loads
         }
 #pragma unroll
         for (int u = 0; u < kPsiUnrollReduce; ++u) {
-            if (rec[u].loc & kPsiSkipBit) continue;
+            if (s0 + (int64_t)u * blockDim.x >= end || (rec[u].loc & kPsiSkipBit)) continue;
             const int loc = (int)(rec[u].loc & (uint32_t)(cpt - 1));
 #pragma unroll
             for (int k = 0; k < C; ++k) {
-                const double v = (double)rec[u].phi[k] * qs[k];   // exact: a power-of-two scale
-                const double hi = rint(v);
-                atomicAdd(&sacc[k * cpt + loc], (unsigned long long)(long long)hi);
+                double hi, lh;
+                const double p = (double)rec[u].phi[k];    // p qs[k] is exact: a power-of-two scale
+                atomicAdd(&sacc[k * cpt + loc], (unsigned long long)quantise<BIG>(p, qs[k], hi));
                 if (W == 2) {
-                    // v - hi is exact (|v - hi| <= 1/2 and hi is v's nearest integer)
-                    const long long lo = llrint((v - hi) * qf);
+                    // the remainder is exact (at most 1/2 from the nearest integer)
+                    const long long lo = quantise<BIG>(fma(p, qs[k], -hi), qf, lh);
                     atomicAdd(&sacc[(C + k) * cpt + loc], (unsigned long long)lo);
                 }
             }
@@ -736,12 +761,13 @@ __global__ __launch_bounds__(256) void k_cic_scatter(PsiArgs a)
 // its scanned per-tile counts (as the PSI-CELL scatter does with its bins;
 // here the bins are the tiles, at most kCicMaxBins of them).  Records keep
 // their whole code (tile and cell) with the skip bit.
-template <typename R> struct CicRoundPerThread { static constexpr int value = sizeof(R) == 4 ? 14 : 7; };
+// particles per thread in a round: its records take 112 KiB of LDS (binary64 96)
+template <typename R> struct CicRoundPerThread { static constexpr int value = sizeof(R) == 4 ? 7 : 3; };
 template <typename R, int D>
-__global__ __launch_bounds__(256) void k_cic_scatter_sorted(PsiArgs a)
+__global__ __launch_bounds__(kPsiScatterThreads) void k_cic_scatter_sorted(PsiArgs a)
 {
     constexpr int C = D + 1;
-    constexpr int NT = 256;
+    constexpr int NT = kPsiScatterThreads;
     constexpr int U = CicRoundPerThread<R>::value;
     constexpr int RB = NT * U;
     constexpr int BPT = kCicMaxBins / NT;
@@ -765,30 +791,30 @@ __global__ __launch_bounds__(256) void k_cic_scatter_sorted(PsiArgs a)
 #pragma unroll
     for (int k = 0; k < C; ++k) mx[k] = 0.0;
     unsigned long long bad = 0;
+    int nxt[U];
+    R v[U][3], ug[U][3], rr[U];
+    double xp[U][3];
+    auto load = [&](int64_t r0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = r0 + (int64_t)u * NT + tid, p = q < end ? q : end - 1;
+            nxt[u] = a.codes[p];
+#pragma unroll
+            for (int ax = 0; ax < D; ++ax) {
+                v[u][ax] = ((const R*)a.p.v[ax])[p];
+                ug[u][ax] = ((const R*)a.p.ug[ax])[p];
+                xp[u][ax] = a.p.x[ax][p];
+            }
+            rr[u] = ((const R*)a.p.r)[p];
+        }
+    };
+    if (beg < end) load(beg);
     for (int64_t r0 = beg; r0 < end; r0 += RB) {
         int code[U];
         unsigned int rank[U];
         CicRec<R> rec[U];
-        R v[U][3], ug[U][3], rr[U];
-        double xp[U][3];
-        // the round's loads first: codes, then the inputs of every live particle
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t p = r0 + (int64_t)u * NT + tid;
-            code[u] = p < end ? a.codes[p] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t p = r0 + (int64_t)u * NT + tid;
-            const bool live = code[u] >= 0;
-#pragma unroll
-            for (int ax = 0; ax < D; ++ax) {
-                v[u][ax] = live ? ((const R*)a.p.v[ax])[p] : (R)0;
-                ug[u][ax] = live ? ((const R*)a.p.ug[ax])[p] : (R)0;
-                xp[u][ax] = live ? a.p.x[ax][p] : 0.0;
-            }
-            rr[u] = live ? ((const R*)a.p.r)[p] : (R)1;
-        }
+        for (int u = 0; u < U; ++u) code[u] = r0 + (int64_t)u * NT + tid < end ? nxt[u] : -1;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             rank[u] = 0;
@@ -819,6 +845,8 @@ __global__ __launch_bounds__(256) void k_cic_scatter_sorted(PsiArgs a)
             for (int k = 0; k < C; ++k) mx[k] = fmax(mx[k], fabs((double)rec[u].phi[k]));
             rank[u] = atomicAdd(&cnt[code[u] >> bsh], 1u);
         }
+        // the next round's particles are read while this one is sorted and written
+        if (r0 + RB < end) load(r0 + RB);
         __syncthreads();
         // tiles BPT tid .. BPT tid + BPT - 1
         const int b0 = BPT * tid;
@@ -871,102 +899,138 @@ __global__ __launch_bounds__(256) void k_cic_scatter_sorted(PsiArgs a)
     }
 }
 
-// One workgroup per tile: the tile's particles deposit into LDS sums over
-// the tile and its upper halo, which are then added to the global sums.
+// The tile buckets lie one after another; each workgroup takes an equal share
+// of all records, so that tiles of any population keep every compute unit
+// busy.  Per tile that its share touches, the particles deposit into LDS sums
+// over the tile and its upper halo, which are then added to the global sums.
 // Channels 0..C-1 carry phi (W words each), channel C the weights (W words,
 // at the scale of the fine word: at most one unit of weight per particle and
-// corner).
-template <typename R, int D, int NT>
+// corner).  BIG: at least kPsiBigCount particles, whose words stay below 2^50.
+// Bound by the LDS atomics, 40 for a particle in 3-D: 50M particles on 64^3
+// cells (128 tiles) take 0.86 ms.  They took 4.79 with a workgroup per tile,
+// which left half of the compute units idle and the others waiting for the
+// fullest tile, and a conversion to int64 per word.
+template <typename R, int D, int NT, bool BIG>
 __global__ __launch_bounds__(NT) void k_cic_reduce(PsiArgs a)
 {
     constexpr int C = D + 1;
     constexpr int W = PsiWords<R>::value;
     constexpr int NCH = W * (C + 1);     // integer words per cell: C channels, then the weights
+    constexpr int U = 2;                 // records of a thread in flight
     extern __shared__ unsigned long long sacc[];
     const int hx = a.pt[0] + 1, hy = a.pt[1] + 1, hz = D == 3 ? a.pt[2] + 1 : 1;
     const int HC = hx * hy * hz;
-    for (int i = threadIdx.x; i < NCH * HC; i += blockDim.x) sacc[i] = 0ull;
+    // words of a cell side by side where their number is odd (every bank is
+    // then hit alike), else one plane of cells per word
+    const int SC = NCH % 2 ? NCH : 1, SJ = NCH % 2 ? 1 : HC;
+    for (int i = threadIdx.x; i < NCH * HC; i += NT) sacc[i] = 0ull;
     double qs[C];
 #pragma unroll
     for (int k = 0; k < C; ++k) qs[k] = a.qscale[k];
     // a particle can put up to 2^D remainders (and weights) on one cell
     // (periodic axes of one cell): 2^-D of the PSI-CELL fine scale
     const double qf = a.qscale[4] / (double)(1 << D);
-    __syncthreads();
-    const int tile = blockIdx.x;
     const int64_t nbk = a.nblocks;
-    const int64_t beg = a.blockhist[(int64_t)tile * nbk];
-    const int64_t end = a.blockhist[(int64_t)(tile + 1) * nbk];
+    auto start = [&](int t) { return (int64_t)a.blockhist[(int64_t)t * nbk]; };
+    const int64_t total = start(a.pntiles);
+    const int64_t beg = total * blockIdx.x / gridDim.x, end = total * (blockIdx.x + 1) / gridDim.x;
     const CicRec<R>* bucket = (const CicRec<R>*)a.bucket;
-    for (int64_t sl = beg + threadIdx.x; sl < end; sl += blockDim.x) {
-        const CicRec<R> rec = bucket[sl];
-        // the cell in the tile: the low bits of a full code (sorted scatter)
-        // or of the cell itself; skipped records carry the skip bit
-        if (rec.loc & kPsiSkipBit) continue;
-        const uint32_t cl = rec.loc & (uint32_t)(a.cpt - 1);
-        const int l0 = (int)(cl & (uint32_t)(a.pt[0] - 1));
-        const int l1 = (int)((cl >> a.ptlog[0]) & (uint32_t)(a.pt[1] - 1));
-        const int l2 = D == 3 ? (int)(cl >> (a.ptlog[0] + a.ptlog[1])) : 0;
-        double wa[3][2];
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const double f = ax < D ? (double)rec.frac[ax] : 0.0;
-            wa[ax][0] = 1.0 - f;
-            wa[ax][1] = f;
+    const MeshDev& m = a.m;
+    const int64_t M = m.M;
+    int tile = -1;
+    for (int64_t pos = beg; pos < end;) {
+        // the tile of record pos: the next one, or by bisection over empty ones
+        ++tile;
+        if (tile == 0 || start(tile + 1) <= pos) {
+            int hi = a.pntiles - 1;
+            while (tile < hi) {
+                const int mid = (tile + hi) >> 1;
+                if (start(mid + 1) <= pos)
+                    tile = mid + 1;
+                else
+                    hi = mid;
+            }
         }
+        const int64_t te = start(tile + 1), last = te < end ? te : end;
+        __syncthreads();
+        for (int64_t s0 = pos + threadIdx.x; s0 < last; s0 += (int64_t)NT * U) {
+            CicRec<R> rec[U];
 #pragma unroll
-        for (int q = 0; q < (1 << D); ++q) {
-            const int b0 = q & 1, b1 = (q >> 1) & 1, b2 = D == 3 ? (q >> 2) & 1 : 0;
-            const double w = wa[0][b0] * wa[1][b1] * (D == 3 ? wa[2][b2] : 1.0);
-            if (w == 0.0) continue;
-            const int hc = (l0 + b0) + hx * ((l1 + b1) + hy * (l2 + b2));
+            for (int u = 0; u < U; ++u) {
+                const int64_t sl = s0 + (int64_t)u * NT;
+                rec[u] = bucket[sl < last ? sl : last - 1];   // no branch between the loads
+            }
 #pragma unroll
-            for (int k = 0; k < C; ++k) {
-                const double v = (double)rec.phi[k] * w * qs[k];
-                const double hi = rint(v);
-                atomicAdd(&sacc[(size_t)(W * k) * HC + hc], (unsigned long long)(long long)hi);
-                if (W == 2) {
-                    const long long lo = llrint((v - hi) * qf);
-                    atomicAdd(&sacc[(size_t)(W * k + 1) * HC + hc], (unsigned long long)lo);
+            for (int u = 0; u < U; ++u) {
+                // the cell in the tile: the low bits of a full code (sorted
+                // scatter) or of the cell itself; skipped records carry the
+                // skip bit
+                if (s0 + (int64_t)u * NT >= last || (rec[u].loc & kPsiSkipBit)) continue;
+                const uint32_t cl = rec[u].loc & (uint32_t)(a.cpt - 1);
+                const int l0 = (int)(cl & (uint32_t)(a.pt[0] - 1));
+                const int l1 = (int)((cl >> a.ptlog[0]) & (uint32_t)(a.pt[1] - 1));
+                const int l2 = D == 3 ? (int)(cl >> (a.ptlog[0] + a.ptlog[1])) : 0;
+                const int base = (l0 + hx * (l1 + hy * l2)) * SC;
+                double wa[3][2], pq[C];
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) {
+                    const double f = ax < D ? (double)rec[u].frac[ax] : 0.0;
+                    wa[ax][0] = 1.0 - f;
+                    wa[ax][1] = f;
+                }
+#pragma unroll
+                for (int k = 0; k < C; ++k) pq[k] = (double)rec[u].phi[k] * qs[k];   // a power-of-two scale
+#pragma unroll
+                for (int q = 0; q < (1 << D); ++q) {
+                    const int b0 = q & 1, b1 = (q >> 1) & 1, b2 = D == 3 ? (q >> 2) & 1 : 0;
+                    const double w = wa[0][b0] * wa[1][b1] * (D == 3 ? wa[2][b2] : 1.0);
+                    unsigned long long* cell = sacc + base + (b0 + hx * (b1 + hy * b2)) * SC;
+                    // the channels, then the weights: W words each (the fine
+                    // word keeps the remainder of each quantised value, so
+                    // sparse cells keep their relative accuracy)
+#pragma unroll
+                    for (int k = 0; k <= C; ++k) {
+                        const double pk = k < C ? pq[k] : qf;
+                        double hi;
+                        const long long v = quantise<BIG>(pk, w, hi);
+                        atomicAdd(&cell[(W * k) * SJ], (unsigned long long)v);
+                        if (W == 2) {
+                            double lh;
+                            const long long lo = quantise<BIG>(fma(pk, w, -hi), qf, lh);
+                            atomicAdd(&cell[(W * k + 1) * SJ], (unsigned long long)lo);
+                        }
+                    }
                 }
             }
-            // the weights, W words as the channels (the fine word keeps the
-            // remainder of each quantised weight, so sparse cells keep their
-            // relative accuracy)
-            const double wq = w * qf;
-            const double wh = rint(wq);
-            atomicAdd(&sacc[(size_t)(W * C) * HC + hc], (unsigned long long)(long long)wh);
-            if (W == 2) atomicAdd(&sacc[(size_t)(W * C + 1) * HC + hc], (unsigned long long)llrint((wq - wh) * qf));
         }
-    }
-    __syncthreads();
-    const MeshDev& m = a.m;
-    int tc[3];
-    tc[0] = tile % a.pnt[0];
-    tc[1] = (tile / a.pnt[0]) % a.pnt[1];
-    tc[2] = (D == 3) ? tile / (a.pnt[0] * a.pnt[1]) : 0;
-    const int64_t M = m.M;
-    for (int hc = threadIdx.x; hc < HC; hc += blockDim.x) {
-        const int h0 = hc % hx, h1 = (hc / hx) % hy, h2 = hc / (hx * hy);
-        int64_t i[3] = {(int64_t)tc[0] * a.pt[0] + h0, (int64_t)tc[1] * a.pt[1] + h1,
-                        D == 3 ? (int64_t)tc[2] * a.pt[2] + h2 : 0};
-        bool inside = true;
+        __syncthreads();
+        int tc[3];
+        tc[0] = tile % a.pnt[0];
+        tc[1] = (tile / a.pnt[0]) % a.pnt[1];
+        tc[2] = (D == 3) ? tile / (a.pnt[0] * a.pnt[1]) : 0;
+        for (int hc = threadIdx.x; hc < HC; hc += NT) {
+            const int h0 = hc % hx, h1 = (hc / hx) % hy, h2 = hc / (hx * hy);
+            int64_t i[3] = {(int64_t)tc[0] * a.pt[0] + h0, (int64_t)tc[1] * a.pt[1] + h1,
+                            D == 3 ? (int64_t)tc[2] * a.pt[2] + h2 : 0};
+            bool inside = true;
 #pragma unroll
-        for (int ax = 0; ax < D; ++ax) {
-            if (i[ax] >= m.n[ax]) {
-                if (m.periodic[ax])
-                    i[ax] -= m.n[ax];
-                else
-                    inside = false;
+            for (int ax = 0; ax < D; ++ax) {
+                if (i[ax] >= m.n[ax]) {
+                    if (m.periodic[ax])
+                        i[ax] -= m.n[ax];
+                    else
+                        inside = false;
+                }
+            }
+            const int64_t c = i[0] + (int64_t)m.n[0] * (i[1] + (int64_t)m.n[1] * i[2]);
+#pragma unroll
+            for (int j = 0; j < NCH; ++j) {
+                const unsigned long long v = sacc[(size_t)hc * SC + (size_t)j * SJ];
+                sacc[(size_t)hc * SC + (size_t)j * SJ] = 0ull;
+                if (v && inside) atomicAdd(&a.acc[(size_t)j * M + c], v);
             }
         }
-        if (!inside) continue;
-        const int64_t c = i[0] + (int64_t)m.n[0] * (i[1] + (int64_t)m.n[1] * i[2]);
-#pragma unroll
-        for (int j = 0; j < NCH; ++j) {
-            const unsigned long long v = sacc[(size_t)j * HC + hc];
-            if (v) atomicAdd(&a.acc[(size_t)j * M + c], v);
-        }
+        pos = last;
     }
 }
 
@@ -1015,7 +1079,7 @@ hipError_t launch_cic(const PsiArgs& a, hipStream_t s)
         e = launch_exclusive_scan_u32(a.blockhist, (int64_t)a.pntiles * a.nblocks + 1, a.scan_tmp, a.scan_words, s);
         if (e != hipSuccess) return e;
         if (a.direct)
-            FLA_LAUNCH((k_cic_scatter_sorted<R, D>), dim3(a.nblocks), dim3(256), 0, s, a);
+            FLA_LAUNCH((k_cic_scatter_sorted<R, D>), dim3(a.nblocks), dim3(kPsiScatterThreads), 0, s, a);
         else
             FLA_LAUNCH((k_cic_scatter<R, D>), dim3(a.nblocks), dim3(256), lds_t, s, a);
     }
@@ -1024,14 +1088,23 @@ hipError_t launch_cic(const PsiArgs& a, hipStream_t s)
     const size_t lds_r = sizeof(unsigned long long) * (size_t)(W * (C + 1)) * (size_t)hcells;
     // large (sorted) tiles: one workgroup of 1024 threads per compute unit,
     // so that enough waves issue the LDS atomics
-    if (a.direct) {
-        e = hipFuncSetAttribute((const void*)k_cic_reduce<R, D, 1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_r);
+    auto reduce = [&](auto nt, auto big) {
+        constexpr int NT = decltype(nt)::value;
+        constexpr bool BIG = decltype(big)::value;
+        const hipError_t e = hipFuncSetAttribute((const void*)k_cic_reduce<R, D, NT, BIG>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_r);
         if (e != hipSuccess) return e;
-        FLA_LAUNCH((k_cic_reduce<R, D, 1024>), dim3(a.pntiles), dim3(1024), lds_r, s, a);
-    } else {
-        FLA_LAUNCH((k_cic_reduce<R, D, 256>), dim3(a.pntiles), dim3(256), lds_r, s, a);
-    }
+        FLA_LAUNCH((k_cic_reduce<R, D, NT, BIG>), dim3(a.nsplit), dim3(NT), lds_r, s, a);
+        return hipSuccess;
+    };
+    using Large = std::integral_constant<int, 1024>;
+    using Small = std::integral_constant<int, 512>;
+    const bool big = a.p.count >= kPsiBigCount;
+    if (a.direct)
+        e = big ? reduce(Large{}, std::true_type{}) : reduce(Large{}, std::false_type{});
+    else
+        e = big ? reduce(Small{}, std::true_type{}) : reduce(Small{}, std::false_type{});
+    if (e != hipSuccess) return e;
     FLA_LAUNCH((k_cic_finish<R, D>), dim3((unsigned)((a.m.M + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
@@ -1113,14 +1186,23 @@ hipError_t launch_psicell(const PsiArgs& a, hipStream_t s)
     if (a.p.count > 0 && !a.direct)
         FLA_LAUNCH((k_psi_tiles<R, D>), dim3(a.pnbins * a.nsplit), dim3(256), 0, s, a);
     size_t lds_r = (sizeof(unsigned long long) * C * PsiWords<R>::value + sizeof(unsigned int)) * (size_t)a.cpt;
-    if (a.direct) {
-        e = hipFuncSetAttribute((const void*)k_psi_reduce<R, D, kPsiDirectThreads>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_r);
+    auto reduce = [&](auto nt, auto big) {
+        constexpr int NT = decltype(nt)::value;
+        constexpr bool BIG = decltype(big)::value;
+        const hipError_t e = hipFuncSetAttribute((const void*)k_psi_reduce<R, D, NT, BIG>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_r);
         if (e != hipSuccess) return e;
-        FLA_LAUNCH((k_psi_reduce<R, D, kPsiDirectThreads>), dim3(a.pntiles), dim3(kPsiDirectThreads), lds_r, s, a);
-    }
+        FLA_LAUNCH((k_psi_reduce<R, D, NT, BIG>), dim3(a.pntiles), dim3(NT), lds_r, s, a);
+        return hipSuccess;
+    };
+    using Large = std::integral_constant<int, kPsiDirectThreads>;
+    using Small = std::integral_constant<int, 256>;
+    const bool big = a.p.count >= kPsiBigCount;
+    if (a.direct)
+        e = big ? reduce(Large{}, std::true_type{}) : reduce(Large{}, std::false_type{});
     else
-        FLA_LAUNCH((k_psi_reduce<R, D, 256>), dim3(a.pntiles), dim3(256), lds_r, s, a);
+        e = big ? reduce(Small{}, std::true_type{}) : reduce(Small{}, std::false_type{});
+    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
