@@ -82,25 +82,31 @@ __device__ inline void two_sum_acc(R& hi, R& lo, R p)
     lo += err;
 }
 
-// waves per workgroup (all work on one tile): four in 3-D; two in 2-D, whose
-// tiles have twice the cells per axis and whose staging tables are larger
-template <int D> struct GatherWaves { static constexpr int value = D == 3 ? 4 : 2; };
+// waves per workgroup (all work on one tile or part): four; two in binary32
+// 2-D, whose tiles have twice the cells per axis and whose staging tables are
+// larger
+template <typename R, int D> struct GatherWaves { static constexpr int value = D == 3 || sizeof(R) == 8 ? 4 : 2; };
 
-// Workgroups per tile (the shape).  With TP = 2 (3-D, binary64) each workgroup
-// owns one half of the tile along x (4 of its 8 sub-blocks), which halves
-// the registers of its sums and its staging space, so that more workgroups
-// share a compute unit, at the cost of scanning and staging every candidate
-// once per half.
+// Workgroups per tile (the shape).  With TP = 2 (binary64) each workgroup owns
+// one half of the tile along x, which halves the registers of its sums and its
+// staging space, so that more workgroups share a compute unit, at the cost of
+// scanning and staging every candidate once per half.  They stage 32 records
+// at a time, two lanes to a record: half the space again, so that two
+// workgroups fit a compute unit instead of one and the binary64 chains of one
+// cover the other's (61 x 47 x 53 cells, 120k trajectories: 382 -> 284 us).  In
+// 2-D, two halves of four waves in place of one tile of two also spread a small
+// mesh over four times the waves (64^2 cells: 87 -> 32 us).
 template <typename R> __host__ __device__ constexpr int tile_parts(int D, int shape)
 {
-    return sizeof(R) == 8 && D == 3 && shape == 0 ? 2 : 1;
+    return sizeof(R) == 8 && shape == 0 ? 2 : 1;
 }
 
 // Waves per SIMD the register allocation is held to (binary32 in 3-D: the
 // sums of eight planes take 120 registers; at three waves the rest spills
-// into the loops, 6.9 instead of 5.0 ms on the 128^3 case).
+// into the loops, 6.9 instead of 5.0 ms on the 128^3 case; binary64: two where
+// the staging space lets two workgroups in).
 template <typename R, int D, int TP> struct GatherOcc {
-    static constexpr int value = sizeof(R) == 4 ? 2 : 1;
+    static constexpr int value = sizeof(R) == 4 || TP == 2 ? 2 : 1;
 };
 
 template <typename R, int D, int TP>
@@ -109,11 +115,12 @@ struct GatherLds {
     using R2 = typename V2<R>::T;
     static constexpr int SB = Geo<D>::SB, NA = D + 2;
     static constexpr int NT = TP == 2 ? D - 1 : D;   // axes staged for both halves (split: y, z)
+    static constexpr int NB = TP == 2 ? kWave / 2 : kWave;   // records staged at a time
     uint32_t cand[kCap];               // compacted candidate record indices
-    R4 tab[kWave][NT][SB];             // {s, e} at in-block position l and l + SB
-    R2 tabs[kWave][TP == 2 ? SB : 1];  // split axis x: {s, e} of the owned half
-    R wts[kWave][NA];                  // {1/h, q/h ...} of each staged record
-    int mask[kWave];                   // sub-blocks holding at least one included pair
+    R4 tab[NB][NT][SB];                // {s, e} at in-block position l and l + SB
+    R2 tabs[NB][TP == 2 ? SB : 1];     // split axis x: {s, e} of the owned half
+    R wts[NB][NA];                     // {1/h, q/h ...} of each staged record
+    int mask[NB];                      // sub-blocks holding at least one included pair
 };
 
 // Per-axis factors of one record for the tile at tile coordinates tc, whose
@@ -127,11 +134,16 @@ struct GatherLds {
 // no sub-block holding an included pair is skipped).
 template <typename R, int D, int TP>
 __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs)[Geo<D>::TE], const int* tc,
-                                            const int soff, const double4 P, const R c2,
+                                            const int soff, const double4 P, const R c2, const int part,
                                             typename V4<R>::T (*tab)[Geo<D>::SB], typename V2<R>::T* tabs)
 {
     using G = Geo<D>;
-    constexpr int TE = G::TE, SB = G::SB, NP = 2 * SB, NSB = G::NSB / TP;
+    constexpr int TE = G::TE, SB = G::SB, NSB = G::NSB / TP;
+    // positions l of a half tile that this lane takes: all of them, or (two
+    // lanes to a record, 32 apart) its half of them
+    constexpr int NL = TP == 2 ? SB / 2 : SB, NP = 2 * NL;
+    const int l0 = TP == 2 ? part * NL : 0;
+    auto whole = [](R v) { return TP == 2 ? fmin(v, __shfl_xor(v, kWave / 2, kWave)) : v; };
     using R4 = typename V4<R>::T;
     using R2 = typename V2<R>::T;
     double x[3] = {P.x, P.y, P.z};
@@ -143,12 +155,12 @@ __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         const bool one = TP == 2 && a == 0;   // one half of this axis, at soff
-        const int np = one ? SB : NP;
+        const int np = one ? NL : NP;
         double d[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             // positions l and l + SB of the sub-blocks, or soff + l
-            const int pp = one ? soff + p : p;
+            const int pp = l0 + (one ? soff + p : p < NL ? p : p - NL + SB);
             d[p] = (p < np) ? xcs[a][pp] - x[a] : 0.0;
         }
         if (m.periodic[a]) {
@@ -156,6 +168,7 @@ __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs
             double dm = 0.0;
 #pragma unroll
             for (int p = 0; p < NP; ++p) dm = fmax(dm, fabs(d[p]));
+            if (TP == 2) dm = fmax(dm, __shfl_xor(dm, kWave / 2, kWave));
             const double L = m.L[a];
             if (dm > 0.5 * L) {
                 if (dm < L) {
@@ -184,7 +197,7 @@ __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs
             const int64_t hcell = home_index(m, a, x[a]);
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                const int pp = one ? soff + p : p;
+                const int pp = l0 + (one ? soff + p : p < NL ? p : p - NL + SB);
                 const bool home = (int64_t)tc[a] * TE + pp == hcell;
                 sv[p] = home ? (R)0 : r_inf<R>();
                 ev[p] = home ? (R)1 : (R)0;
@@ -192,25 +205,25 @@ __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs
         }
         R mlo = r_inf<R>(), mhi = r_inf<R>();
 #pragma unroll
-        for (int l = 0; l < SB; ++l) {
+        for (int l = 0; l < NL; ++l) {
             if (one) {
                 R2 t2;
                 t2.x = sv[l];
                 t2.y = ev[l];
-                tabs[l] = t2;
+                tabs[l0 + l] = t2;
             } else {
                 R4 t4;
                 t4.x = sv[l];
                 t4.y = ev[l];
-                t4.z = sv[l + SB];
-                t4.w = ev[l + SB];
-                tab[TP == 2 ? a - 1 : a][l] = t4;
-                mhi = fmin(mhi, sv[l + SB]);
+                t4.z = sv[l + NL];
+                t4.w = ev[l + NL];
+                tab[TP == 2 ? a - 1 : a][l0 + l] = t4;
+                mhi = fmin(mhi, sv[l + NL]);
             }
             mlo = fmin(mlo, sv[l]);
         }
-        mn[a][0] = mlo;
-        mn[a][1] = mhi;
+        mn[a][0] = whole(mlo);
+        mn[a][1] = whole(mhi);
     }
     // visit mask: the sub-block can hold an included pair (the sum of
     // the per-axis minima passes; binary32/64 sums are monotone in each
@@ -494,7 +507,7 @@ template <int MODE, bool COUNT, int PLAN>
 __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile)
 {
     using L = PlaneLds;
-    constexpr int W = GatherWaves<3>::value, TE = Geo<3>::TE, ZP = TE, C = 4, NA = 5;
+    constexpr int W = GatherWaves<float, 3>::value, TE = Geo<3>::TE, ZP = TE, C = 4, NA = 5;
     constexpr int NB = L::NB, HZ = ZP / 2, GR = kPlaneRecs;
     constexpr bool kGeneral = MODE == kNwGeneral;
     static_assert(GR * ZP == 16, "one row of lanes per group");
@@ -931,10 +944,10 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
 __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
 {
-    constexpr int kGatherWaves = GatherWaves<D>::value;
+    constexpr int kGatherWaves = GatherWaves<R, D>::value;
     using G = Geo<D>;
-    static_assert(TP == 1 || D == 3, "tiles are split along x in 3-D only");
     constexpr int TE = G::TE, SB = G::SB, NSB = G::NSB / TP, C = D + 1, NA = C + 1;
+    constexpr int NB = GatherLds<R, D, TP>::NB, LPR = kWave / NB;   // records a batch, lanes that stage one
     constexpr int NT = GatherLds<R, D, TP>::NT;
     constexpr bool kComp = sizeof(R) == 4;
     using R4 = typename V4<R>::T;
@@ -1037,21 +1050,23 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
     const uint64_t ltmask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     __syncthreads();
 
-    // ---- one batch of n <= 64 staged candidates of this wave
+    // ---- one batch of n <= NB staged candidates of this wave
     auto process = [&](int n) {
         wave_sync();
-        if (lane < n) {
-            uint32_t p = my.cand[lane];
+        const int rec = lane % NB;
+        if (rec < n) {
+            uint32_t p = my.cand[rec];
             double4 P = g.rpos[p];
             const R* w = (const R*)g.rw + (size_t)p * kRecW;
 #pragma unroll
-            for (int k = 0; k < NA; ++k) my.wts[lane][k] = w[k];
-            my.mask[lane] = stage_record<R, D, TP>(m, xcs, tc, soff, P, c2, my.tab[lane], my.tabs[lane]);
+            for (int k = 0; k < NA; ++k) my.wts[rec][k] = w[k];
+            my.mask[rec] =
+                stage_record<R, D, TP>(m, xcs, tc, soff, P, c2, LPR == 2 ? lane / NB : 0, my.tab[rec], my.tabs[rec]);
         }
         wave_sync();
         // every lane keeps the mask of one staged record (read with readlane,
         // no LDS round trip)
-        const int maskv = (lane < n) ? my.mask[lane] : 0;
+        const int maskv = (lane < n) ? my.mask[lane < NB ? lane : 0] : 0;
         // one sub-block of one record: the per-pair inclusion test, then the
         // denominator multiply-add and the C channel multiply-adds.  In
         // binary32 the channels go to one v_mfma_f32_4x4x1_16b_f32: with A
@@ -1068,8 +1083,10 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
                 const int by = b & 1, bz = (b >> 1) & 1;
                 s = ts.x + (by ? t[0].z : t[0].x);
                 ew = ts.y * (by ? t[0].w : t[0].y);
-                s = s + (bz ? t[1].z : t[1].x);
-                ew = ew * (bz ? t[1].w : t[1].y);
+                if constexpr (D == 3) {
+                    s = s + (bz ? t[1].z : t[1].x);
+                    ew = ew * (bz ? t[1].w : t[1].y);
+                }
             } else {
                 const int bx = b & 1, by = (b >> 1) & 1, bz = (b >> 2) & 1;
                 s = (bx ? t[0].z : t[0].x) + (by ? t[1].z : t[1].x);
@@ -1201,10 +1218,10 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
             uint64_t bal = __ballot(ok);
             if (ok) my.cand[ncand + __popcll(bal & ltmask)] = p;
             ncand += __popcll(bal);
-            if (ncand >= kWave) {
-                process(kWave);
-                int rem = ncand - kWave;
-                uint32_t mv = (lane < rem) ? my.cand[kWave + lane] : 0u;
+            while (ncand >= NB) {
+                process(NB);
+                int rem = ncand - NB;
+                uint32_t mv = (lane < rem) ? my.cand[NB + lane] : 0u;
                 wave_sync();
                 if (lane < rem) my.cand[lane] = mv;
                 ncand = rem;
@@ -1300,7 +1317,7 @@ __device__ __forceinline__ void gather_work(const GatherArgs& g, const int work)
 // workgroup that finishes early starts the next item at once (128^3: 4.93 ->
 // 4.80 ms).  Which workgroup computes an item does not change its results.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
-static __global__ __launch_bounds__(kWave * GatherWaves<D>::value, (GatherOcc<R, D, TP>::value)) void k_gather(GatherArgs g)
+static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherOcc<R, D, TP>::value)) void k_gather(GatherArgs g)
 {
     const int total = g.m.ntiles * TP;
     __shared__ int s_slot;
@@ -1412,7 +1429,7 @@ static __device__ inline int batch_work_item(int bid, int nwork, int chunk)
 // 37.5 against 38.4 ms).  Which workgroup computes an item does not change
 // its results.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
-static __global__ __launch_bounds__(kWave * GatherWaves<D>::value, (GatherOcc<R, D, TP>::value)) void k_gather_batch(
+static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherOcc<R, D, TP>::value)) void k_gather_batch(
     const BatchItem* __restrict__ items, int nsnap, int nwork, int chunk, uint32_t* __restrict__ queue)
 {
     __shared__ int s_slot;
@@ -1459,7 +1476,7 @@ static void launch_plan(const GatherArgs& g, int plan, dim3 grid, dim3 block, hi
 template <typename R, int D, int TP>
 static int64_t resident_workgroups(int ncu)
 {
-    return (int64_t)(ncu > 0 ? ncu : 1) * GatherOcc<R, D, TP>::value * 4 / GatherWaves<D>::value;
+    return (int64_t)(ncu > 0 ? ncu : 1) * GatherOcc<R, D, TP>::value * 4 / GatherWaves<R, D>::value;
 }
 
 template <typename R, int D, int MODE, bool COUNT, int TP>
@@ -1471,7 +1488,7 @@ static void launch_batch_plan(const BatchItem* items, int nsnap, int nwork, int 
     const int64_t total = (int64_t)nwork * TP;
     if (nb > total) nb = total;
     if (nb < 1) nb = 1;
-    dim3 grid((unsigned)nb), block(kWave * GatherWaves<D>::value);
+    dim3 grid((unsigned)nb), block(kWave * GatherWaves<R, D>::value);
     constexpr int kFinest = finest_plan<R, D>();
     switch (plan) {
     case 1: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 1, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
@@ -1508,13 +1525,12 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
     // the XCD counters start at zero (a fill kernel: the launch may be captured)
     hipError_t e = launch_fill_u32(queue, kXcds, 0u, s);
     if (e != hipSuccess) return e;
-    if constexpr (tile_parts<R>(D, 0) == 2) {
-        if (tile_parts<R>(D, shape) == 2) {
-            launch_batch_shape<R, D, 2>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu, s);
-            return hipGetLastError();
-        }
-    }
-    launch_batch_shape<R, D, 1>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu, s);
+    // in 2-D there is no other shape than the first
+    if (D == 2 || shape == 0)
+        launch_batch_shape<R, D, tile_parts<R>(D, 0)>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu, s);
+    else
+        launch_batch_shape<R, D, tile_parts<R>(D, D == 3)>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu,
+                                                           s);
     return hipGetLastError();
 }
 
@@ -1530,7 +1546,7 @@ static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count,
     if (fit < nb) nb = fit;
     hipError_t e = launch_fill_u32(g.queue, kXcds, 0u, s);
     if (e != hipSuccess) return e;
-    dim3 grid((unsigned)nb), block(kWave * GatherWaves<D>::value);
+    dim3 grid((unsigned)nb), block(kWave * GatherWaves<R, D>::value);
     const bool general = g.m.edges[0] || g.m.edges[1] || g.m.edges[2];
     if (mode == FLA_NW && general) {
         if (count)
@@ -1556,10 +1572,9 @@ hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_cod
 {
     if (g.m.ntiles <= 0) return hipSuccess;
     const int plan = plan_code % kGatherPlans, shape = plan_code / kGatherPlans;
-    if constexpr (tile_parts<R>(D, 0) == 2) {
-        if (tile_parts<R>(D, shape) == 2) return launch_gather_shape<R, D, 2>(g, mode, count, plan, s);
-    }
-    return launch_gather_shape<R, D, 1>(g, mode, count, plan, s);
+    // in 2-D there is no other shape than the first
+    if (D == 2 || shape == 0) return launch_gather_shape<R, D, tile_parts<R>(D, 0)>(g, mode, count, plan, s);
+    return launch_gather_shape<R, D, tile_parts<R>(D, D == 3)>(g, mode, count, plan, s);
 }
 
 }  // namespace flp
