@@ -488,7 +488,8 @@ __device__ __forceinline__ bool near_tile(const MeshDev& m, const double4 P, con
     return acc <= filt2;
 }
 
-// The work of one workgroup in binary32 and 3-D: one tile.  The four waves
+// The work of one workgroup in binary32 and 3-D: the planes of `own` (a bit
+// per two) of one tile.  The four waves
 // take the chunks of 64 candidates in turn and keep their own sums.
 //
 // What bounds it: instruction issue.  A plane of one record takes 22 cycles (a
@@ -504,13 +505,14 @@ __device__ __forceinline__ bool near_tile(const MeshDev& m, const double4 P, con
 // trajectories on 128^3 cells 4.79 -> 3.75 ms (24.8 TFLOP/s of the 15 flops
 // per included pair), 32.8M on 256^3 279.6 -> 203 ms (39 TFLOP/s).
 template <int MODE, bool COUNT, int PLAN>
-__device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile)
+__device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile, const int share, const int shares)
 {
     using L = PlaneLds;
     constexpr int W = GatherWaves<float, 3>::value, TE = Geo<3>::TE, ZP = TE, C = 4, NA = 5;
     constexpr int NB = L::NB, HZ = ZP / 2, GR = kPlaneRecs;
     constexpr bool kGeneral = MODE == kNwGeneral;
     static_assert(GR * ZP == 16, "one row of lanes per group");
+    const uint32_t own = ((1u << (ZP / 2 / shares)) - 1u) << (share * (ZP / 2 / shares));
     static_assert(sizeof(L) * W >= sizeof(double) * W * 4 * NA * kWave, "four planes of sums must fit");
     __shared__ L lds[W];
     __shared__ RunTable runs;
@@ -716,6 +718,8 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
                 reach[q] = (uint32_t)any;
                 reach[q + 2] = (uint32_t)(any >> 32);
             }
+#pragma unroll
+            for (int h = 0; h < ZP / 2; ++h) reach[h] = own >> h & 1 ? reach[h] : 0u;
         }
         wave_sync();
         // the next group's words are read while the current group is summed
@@ -902,7 +906,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
             for (int k = 0; k < NA; ++k) red[((wave * 4 + u) * NA + k) * kWave + lane] = tot[z0 + u][k];
         __syncthreads();
         const int64_t cz = (int64_t)tc[2] * TE + z0 + wave;
-        if (in_xy && cz < m.n[2]) {
+        if (in_xy && cz < m.n[2] && (own >> ((z0 + wave) / 2) & 1)) {
             const int64_t lin = cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * cz);
             double sum[NA];
 #pragma unroll
@@ -928,6 +932,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
         unsigned long long npairs = 0;
 #pragma unroll
         for (int z = 0; z < ZP; ++z) {
+            if (!(own >> (z / 2) & 1)) continue;
             npairs += cnt[z];
             const int64_t cz = (int64_t)tc[2] * TE + z;
             if (g.pairs && cnt[z] && in_xy && cz < m.n[2])
@@ -939,10 +944,10 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
     }
 }
 
-// The work of one workgroup: every cell of its part `work % TP` of tile
-// `work / TP` of the mesh of g.
+// The work of one workgroup: the sub-blocks of its share (every one
+// where `shares` is 1) of part `work % TP` of tile `work / TP` of the mesh of g.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
-__device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
+__device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work, const int share, const int shares)
 {
     constexpr int kGatherWaves = GatherWaves<R, D>::value;
     using G = Geo<D>;
@@ -957,6 +962,8 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
                   "reduction buffer must fit in the staging space");
     __shared__ L lds[kGatherWaves];
     __shared__ double xcs[D][TE];
+
+    const int own = ((1 << (NSB / shares)) - 1) << (share * (NSB / shares));
 
     const MeshDev& m = g.m;
     const int lane = threadIdx.x % kWave;
@@ -1115,7 +1122,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
         // test); in 2-D, 1 and 2 evaluate the whole tile.  All plans add the
         // same products; a skipped sub-block only saves additions of zero.
         auto accumulate = [&](int e, const R4* t, const R2& ts, const R* wv, float wq) {
-            const int mk = __builtin_amdgcn_readlane(maskv, e);
+            const int mk = __builtin_amdgcn_readlane(maskv, e) & own;
             if (mk == 0) return;
             if (PLAN == 3 || (D == 2 && PLAN != 0) || (PLAN == 2 && NSB == 4)) {
 #pragma unroll
@@ -1261,7 +1268,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
     // ---- epilogue: divide (NW) or scale by 1/V_c (deposition), sign, scale
     for (int b = wave; b < NSB; b += kGatherWaves) {
         int64_t lin;
-        if (!cell_of(b, lin)) continue;
+        if (!(own >> b & 1) || !cell_of(b, lin)) continue;
         double tot[NA];
 #pragma unroll
         for (int k = 0; k < NA; ++k) {
@@ -1290,6 +1297,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
         unsigned long long npairs = 0;
 #pragma unroll
         for (int b = 0; b < NSB; ++b) {
+            if (!(own >> b & 1)) continue;
             npairs += cntb[b];
             int64_t lin;
             if (g.pairs && cntb[b] && cell_of(b, lin)) atomicAdd(&g.pairs[lin], cntb[b]);
@@ -1300,14 +1308,16 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work)
     }
 }
 
-// Work item `work` by the body of its precision and dimension.
+// Share `share` of `shares` of work item `work`, by the body of its precision
+// and dimension.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
-__device__ __forceinline__ void gather_work(const GatherArgs& g, const int work)
+__device__ __forceinline__ void gather_work(const GatherArgs& g, const int work, const int share = 0,
+                                            const int shares = 1)
 {
     if constexpr (sizeof(R) == 4 && D == 3)
-        gather_planes<MODE, COUNT, PLAN>(g, work);
+        gather_planes<MODE, COUNT, PLAN>(g, work, share, shares);
     else
-        gather_tile<R, D, MODE, COUNT, PLAN, TP>(g, work);
+        gather_tile<R, D, MODE, COUNT, PLAN, TP>(g, work, share, shares);
 }
 
 // Slot b of the launch belongs to XCD b % kXcds and computes the work item
@@ -1332,6 +1342,18 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
         w = g.order[w];
         gather_work<R, D, MODE, COUNT, PLAN, TP>(g, w);
     }
+}
+
+// Every share of every part of every tile with a workgroup of its own (small
+// meshes).  A kernel beside the one above, which pays 2% for the shares on the
+// 128^3 case; the plan that skips most finely, since a share skips the cells of
+// the others.
+template <typename R, int D, int MODE, bool COUNT, int TP>
+static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherOcc<R, D, TP>::value)) void k_gather_small(
+    GatherArgs g, int shares)
+{
+    const int w = xcd_remap(blockIdx.x, g.m.ntiles * TP * shares);
+    gather_work<R, D, MODE, COUNT, (sizeof(R) == 4 && D == 3 ? 1 : 0), TP>(g, w / shares, w % shares, shares);
 }
 
 // Estimated work of every tile: the number of candidate records its scan
@@ -1534,37 +1556,52 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
     return hipGetLastError();
 }
 
+// Where every part of every tile has a workgroup at once, their order is
+// nothing and needs neither costs nor counters (three launches); and where
+// compute units would be left idle, up to four workgroups share a part's cells:
+// each scans and stages the same candidates as one would and evaluates its own
+// planes or sub-blocks of them, so the sums keep their order and their bits.
+// Whole calls with and without: 64^2 cells in binary64 107 -> 93 us, in
+// binary32 140 -> 111; 32^3 in binary32 with 100k trajectories 391 -> 343.
+template <typename R, int D, int MODE, bool COUNT, int TP>
+static bool launch_small(const GatherArgs& g, hipStream_t s)
+{
+    constexpr int NSB = sizeof(R) == 4 && D == 3 ? 4 : Geo<D>::NSB / TP, most = NSB < 4 ? NSB : 4;
+    const int64_t fit = resident_workgroups<R, D, TP>(g.ncu), parts = (int64_t)g.m.ntiles * TP;
+    if (parts > fit) return false;
+    int shares = 1;
+    while (2 * shares <= most && parts * 2 * shares <= fit) shares *= 2;
+    FLA_LAUNCH((k_gather_small<R, D, MODE, COUNT, TP>), dim3((unsigned)(parts * shares)),
+               dim3(kWave * GatherWaves<R, D>::value), 0, s, g, shares);
+    return true;
+}
+
 template <typename R, int D, int TP>
 static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, hipStream_t s)
 {
-    FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
-    FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP, g.order);
-    // as many workgroups as the compute units hold at once; the XCD
-    // counters start at zero (a fill kernel: the launch may be captured)
-    int64_t nb = (int64_t)g.m.ntiles * TP;
-    const int64_t fit = resident_workgroups<R, D, TP>(g.ncu);
-    if (fit < nb) nb = fit;
-    hipError_t e = launch_fill_u32(g.queue, kXcds, 0u, s);
-    if (e != hipSuccess) return e;
-    dim3 grid((unsigned)nb), block(kWave * GatherWaves<R, D>::value);
     const bool general = g.m.edges[0] || g.m.edges[1] || g.m.edges[2];
-    if (mode == FLA_NW && general) {
-        if (count)
-            launch_plan<R, D, kNwGeneral, true, TP>(g, plan, grid, block, s);
-        else
-            launch_plan<R, D, kNwGeneral, false, TP>(g, plan, grid, block, s);
-    } else if (mode == FLA_NW) {
-        if (count)
-            launch_plan<R, D, FLA_NW, true, TP>(g, plan, grid, block, s);
-        else
-            launch_plan<R, D, FLA_NW, false, TP>(g, plan, grid, block, s);
-    } else {
-        if (count)
-            launch_plan<R, D, FLA_DEPOSIT, true, TP>(g, plan, grid, block, s);
-        else
-            launch_plan<R, D, FLA_DEPOSIT, false, TP>(g, plan, grid, block, s);
-    }
-    return hipGetLastError();
+    auto launch = [&](auto modec, auto countc) -> hipError_t {
+        constexpr int MODE = decltype(modec)::value;
+        constexpr bool COUNT = decltype(countc)::value;
+        if (launch_small<R, D, MODE, COUNT, TP>(g, s)) return hipGetLastError();
+        FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
+        FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP,
+                   g.order);
+        // as many workgroups as the compute units hold at once; the XCD
+        // counters start at zero (a fill kernel: the launch may be captured)
+        int64_t nb = (int64_t)g.m.ntiles * TP;
+        const int64_t fit = resident_workgroups<R, D, TP>(g.ncu);
+        if (fit < nb) nb = fit;
+        const hipError_t e = launch_fill_u32(g.queue, kXcds, 0u, s);
+        if (e != hipSuccess) return e;
+        launch_plan<R, D, MODE, COUNT, TP>(g, plan, dim3((unsigned)nb), dim3(kWave * GatherWaves<R, D>::value), s);
+        return hipGetLastError();
+    };
+    auto counted = [&](auto modec) {
+        return count ? launch(modec, std::true_type{}) : launch(modec, std::false_type{});
+    };
+    if (mode != FLA_NW) return counted(std::integral_constant<int, FLA_DEPOSIT>{});
+    return general ? counted(std::integral_constant<int, kNwGeneral>{}) : counted(std::integral_constant<int, FLA_NW>{});
 }
 
 template <typename R, int D>
