@@ -431,11 +431,18 @@ fla_status project_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, const 
     uint32_t *skeys, *svals;
     {
         StageTimer tm(ctx, 1, s);
-        HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, N, key_bits, hist, hist_w, scan, scan_w, s, &in_alt));
-        skeys = in_alt ? keys2 : keys;
-        svals = in_alt ? vals2 : vals;
-        HIP_OK(launch_bucket_bounds(skeys, N, nb, bstart, s));
-        HIP_OK(launch_max_class(bstart, m.ntiles, ctx->stats, s));
+        if (sort_is_small(N, nb)) {
+            skeys = keys;
+            svals = vals;
+            HIP_OK(launch_sort_small(keys, vals, N, key_bits, nb, m.ntiles, bstart, ctx->stats + ST_MAXCLASS, s));
+        } else {
+            HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, N, key_bits, hist, hist_w, scan, scan_w, s, &in_alt,
+                                    (uint32_t*)rpos, 8 * N));
+            skeys = in_alt ? keys2 : keys;
+            svals = in_alt ? vals2 : vals;
+            HIP_OK(launch_bucket_bounds(skeys, N, nb, bstart, s));
+            HIP_OK(launch_max_class(bstart, m.ntiles, ctx->stats, s));
+        }
         HIP_OK(launch_permute<R>(svals, N, rpos_u, rw_u, rpos, rw, deposit ? 0 : 1, s));
     }
     if (deposit) {
@@ -639,7 +646,8 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
         {
             StageTimer tm(ctx, 1, q);
             bool in_alt = false;
-            HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, total, key_bits, hist, hist_w, scan, scan_w, q, &in_alt));
+            HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, total, key_bits, hist, hist_w, scan, scan_w, q, &in_alt,
+                                    (uint32_t*)rpos, 8 * total));
             const uint32_t* skeys = in_alt ? keys2 : keys;
             const uint32_t* svals = in_alt ? vals2 : vals;
             HIP_OK(launch_bucket_bounds(skeys, total, nb, bstart, q));
@@ -2201,7 +2209,8 @@ fla_status project_cells_impl(fla_ctx* ctx, const fla_cell_index* ix, const Traj
     {
         StageTimer tm(ctx, 1, s);
         bool in_alt = false;
-        HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, N, key_bits, hist, hist_w, scan, scan_w, s, &in_alt));
+        HIP_OK(radix_sort_pairs(keys, vals, keys2, vals2, N, key_bits, hist, hist_w, scan, scan_w, s, &in_alt,
+                                (uint32_t*)rpos, 8 * N));
         const uint32_t* skeys = in_alt ? keys2 : keys;
         const uint32_t* svals = in_alt ? vals2 : vals;
         HIP_OK(launch_bucket_bounds(skeys, N, nb, bstart, s));

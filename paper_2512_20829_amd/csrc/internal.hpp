@@ -313,7 +313,11 @@ int64_t scan_tmp_words(int64_t n);
 hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                             int64_t n, int key_bits, uint32_t* hist, int64_t hist_words,
                             uint32_t* scan_tmp, int64_t scan_tmp_words_, hipStream_t s,
-                            bool* result_in_alt);
+                            bool* result_in_alt, uint32_t* spare = nullptr, int64_t spare_words = 0);
 int64_t radix_hist_words(int64_t n);
+// Few keys and buckets: sort, bucket bounds and largest class in one launch, in place.
+bool sort_is_small(int64_t n, uint32_t nb);
+hipError_t launch_sort_small(uint32_t* keys, uint32_t* vals, int64_t n, int key_bits, uint32_t nb, int per_class,
+                             uint32_t* bstart, unsigned long long* max_class, hipStream_t s);
 
 }  // namespace flp
