@@ -1,5 +1,7 @@
 // Per-trajectory prepass, bucket bounds, record permutation and the
 // per-trajectory normaliser of the conservative deposition mode.
+#include <type_traits>
+
 #include "internal.hpp"
 #include "kernels.hpp"
 #include "prepass.hpp"
@@ -23,20 +25,21 @@ __device__ inline void prepass_one(const TrajDev& t, const MeshDev& m, const Phy
 // independent chains to interleave (0.317 -> 0.150 ms for 2M trajectories
 // from one to four).
 constexpr int kPrepassPerThread = 4;
+constexpr int64_t kPrepassFew = 1 << 15;
 static_assert(kPrepassPerThread < 8, "wave_count_sum takes per-lane counts below 8");
 
-// kPrepassPerThread trajectories of one snapshot per thread, blockDim apart.
-template <typename R, int D>
+// PT trajectories of one snapshot per thread, blockDim apart.
+template <typename R, int D, int PT>
 __global__ __launch_bounds__(256) void k_prepass(TrajDev t, MeshDev m, PhysDev ph, const float* hfac,
                                                  int deposit, uint32_t* keys, uint32_t* vals,
                                                  double4* rpos, R* rw, double* qd,
                                                  unsigned long long* stats)
 {
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x * kPrepassPerThread + threadIdx.x;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x * PT + threadIdx.x;
     const uint32_t sentinel = (uint32_t)kClasses * (uint32_t)m.ntiles;
     unsigned long long skipped = 0, nosup = 0;   // counts over the thread's trajectories
 #pragma unroll
-    for (int u = 0; u < kPrepassPerThread; ++u) {
+    for (int u = 0; u < PT; ++u) {
         const int64_t i = i0 + (int64_t)u * blockDim.x;
         if (i < t.count)
             prepass_one<R, D>(t, m, ph, hfac, deposit, i, i, 0u, sentinel, keys, vals, rpos, rw, qd, skipped, nosup);
@@ -339,10 +342,20 @@ hipError_t launch_prepass(const TrajDev& t, const MeshDev& m, const PhysDev& ph,
                           double* qd, unsigned long long* stats, hipStream_t s)
 {
     if (t.count == 0) return hipSuccess;
-    const int64_t per_block = 256 * kPrepassPerThread;
-    unsigned nb = (unsigned)((t.count + per_block - 1) / per_block);
-    FLA_LAUNCH((k_prepass<R, D>), dim3(nb), dim3(256), 0, s, t, m, ph, hfac, deposit, keys, vals,
-                       rpos, rw, qd, stats);
+    // few trajectories: one per thread, so that their chains run side by side
+    // instead of four after another on a few compute units (4096 in binary64:
+    // 13.5 -> 5.5 us; at 120k four per thread are faster, 26 us against 31)
+    auto run = [&](auto per) {
+        constexpr int PT = decltype(per)::value;
+        const int64_t per_block = 256 * PT;
+        const unsigned nb = (unsigned)((t.count + per_block - 1) / per_block);
+        FLA_LAUNCH((k_prepass<R, D, PT>), dim3(nb), dim3(256), 0, s, t, m, ph, hfac, deposit, keys, vals, rpos, rw, qd,
+                   stats);
+    };
+    if (t.count <= kPrepassFew)
+        run(std::integral_constant<int, 1>{});
+    else
+        run(std::integral_constant<int, kPrepassPerThread>{});
     return hipGetLastError();
 }
 
