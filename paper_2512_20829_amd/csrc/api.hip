@@ -738,6 +738,9 @@ fla_status psicell_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, double
     a.cptlog = a.ptlog[0] + a.ptlog[1] + a.ptlog[2];
     a.nblocks = kPsiBlocks;
     a.direct = direct ? 1 : 0;
+    // the order of the tiles costs 15 us, what it gains in the reduce at some 2^24
+    // particles (a tenth of 0.12 ms)
+    a.tile_order = direct && t.count >= (int64_t(1) << 24) ? 1 : 0;
     a.binlog = direct ? 0 : kPsiTilesPerBinLog;
     a.pnbins = direct ? a.pntiles : (a.pntiles + kPsiTilesPerBin - 1) / kPsiTilesPerBin;
     // about 2048 workgroups in the tile pass

@@ -140,7 +140,9 @@ struct PsiArgs {
     int direct;                  // the scatter writes the tile buckets itself (bins are tiles; no tile pass)
     int nsplit;                  // workgroups per bin in the tile pass; of the whole CIC reduction
     unsigned int* binhist;       // pnbins * nblocks + 1, scanned in place
-    unsigned int* tcursor;       // pntiles: next free slot of each tile bucket
+    unsigned int* tcursor;       // pntiles: next free slot of each tile bucket, or the tiles in
+                                 // the order that the reduce takes them (tile_order)
+    int tile_order;              // direct box counting: tiles by falling population
     void* binned;                // records grouped by bin (loc = code, top bit = skip)
     void* bucket;                // records grouped by tile (loc = cell in tile or kPsiSkip)
     unsigned long long* blockmax; // nblocks x C bit patterns of per-block max |phi_k|
