@@ -443,7 +443,7 @@ fla_status project_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, const 
             HIP_OK(launch_bucket_bounds(skeys, N, nb, bstart, s));
             HIP_OK(launch_max_class(bstart, m.ntiles, ctx->stats, s));
         }
-        HIP_OK(launch_permute<R>(svals, N, rpos_u, rw_u, rpos, rw, deposit ? 0 : 1, s));
+        HIP_OK(launch_permute<R>(svals, N, rpos_u, rw_u, rpos, rw, deposit ? 0 : 1, bstart + nb, ctx->stats, s));
     }
     if (deposit) {
         StageTimer tm(ctx, 2, s);
@@ -652,7 +652,7 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
             const uint32_t* svals = in_alt ? vals2 : vals;
             HIP_OK(launch_bucket_bounds(skeys, total, nb, bstart, q));
             HIP_OK(launch_max_class_batch(dev_items, nsnap, bstart, ctx->stats, q));
-            HIP_OK(launch_permute<R>(svals, total, rpos_u, rw_u, rpos, rw, 1, q));
+            HIP_OK(launch_permute<R>(svals, total, rpos_u, rw_u, rpos, rw, 1, bstart + nb, ctx->stats, q));
         }
         for (int i = 0; i < nsnap; ++i)
             if (outs[i].pairs) HIP_OK(launch_fill_u32(outs[i].pairs, md[i].M, 0u, q));
@@ -2218,7 +2218,7 @@ fla_status project_cells_impl(fla_ctx* ctx, const fla_cell_index* ix, const Traj
         const uint32_t* svals = in_alt ? vals2 : vals;
         HIP_OK(launch_bucket_bounds(skeys, N, nb, bstart, s));
         HIP_OK(launch_max_class(bstart, ix->g.nbuckets, ctx->stats, s));
-        HIP_OK(launch_permute<R>(svals, N, rpos_u, rw_u, rpos, rw, 1, s));
+        HIP_OK(launch_permute<R>(svals, N, rpos_u, rw_u, rpos, rw, 1, bstart + nb, ctx->stats, s));
     }
     CellsGatherArgs a{};
     a.g = ix->g;

@@ -721,6 +721,63 @@ __global__ __launch_bounds__(kWave, 2) void k_cells_gather(CellsGatherArgs a)
             wave_pairs += np[u];
         }
     }
+    // the weights beyond the range of R (split_over), to the cells that include
+    // their records: infinities, which leave nothing of the finite sums
+    if (a.stats[ST_OVER]) {
+        R over[CPL][C + 1];
+        bool hit[CPL] = {false, false};
+#pragma unroll
+        for (int u = 0; u < CPL; ++u)
+#pragma unroll
+            for (int q = 0; q <= C; ++q) over[u][q] = 0;
+        for (int f = 0; f < nrun; ++f) {
+            uint32_t j0, j1;
+            run_of(f, j0, j1);
+            for (uint32_t p0 = j0; p0 < j1; p0 += kWave) {
+                const uint32_t p = p0 + lane;
+                const int code = p < j1 ? (int)((const R*)a.rw)[(int64_t)p * kRecW + kRecOver] : 0;
+                for (uint64_t bits = __ballot(code != 0); bits; bits &= bits - 1) {
+                    const int e = __builtin_ctzll(bits);
+                    const int oc = __builtin_amdgcn_readlane(code, e);
+                    const double4 P = a.rpos[p0 + e];
+                    const double px[3] = {P.x, P.y, P.z};
+#pragma unroll
+                    for (int u = 0; u < CPL; ++u) {
+                        R ss = 0;
+#pragma unroll
+                        for (int ax = 0; ax < D; ++ax) {
+                            double d = xc[u][ax] - px[ax];
+                            if (a.g.periodic[ax]) d = min_image(d, a.g.L[ax]);
+                            const R s = (R)scaled_sq(d, P.w);
+                            ss = ax ? ss + s : s;
+                        }
+                        if (ss <= c2) {
+                            hit[u] = true;
+#pragma unroll
+                            for (int q = 0; q <= C; ++q)
+                                if ((oc >> (2 * q)) & 3) over[u][q] += gauss_factor(ss) * over_weight<R>(oc, q);
+                        }
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < CPL; ++u) {
+            if (!act[u] || !hit[u]) continue;
+            const int p = first + u * kWave + lane;
+            const uint32_t cell = a.perm[p];
+            const double f = -a.scale * (a.use_vol ? a.vol[p] : 1.0);
+            const bool over_den = over[u][0] != (R)0;
+            const double den = over_den ? (double)over[u][0] : 1.0;
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const double num = (double)over[u][1 + q];
+                if (num == 0.0 && !over_den) continue;
+                ((R*)a.out[q])[cell] = (R)(den > 0.0 ? f * (num / den) : 0.0);
+            }
+            if (over_den && a.den) ((R*)a.den)[cell] = over[u][0];
+        }
+    }
     if (COUNT) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) wave_pairs += __shfl_xor(wave_pairs, o, kWave);

@@ -385,6 +385,69 @@ __device__ __forceinline__ bool candidate_ok(const MeshDev& m, const double4 P, 
     return acc <= filt2;
 }
 
+// Adds the weights beyond the range of R (split_over) to the fields of the lane's
+// cell `lin` with indices cidx, where it includes their records: infinities,
+// which leave nothing of the finite sums.  Called by whole waves, after the cells
+// have been written, only where a record of the call has an over code.
+template <typename R, int D, int MODE>
+__device__ __forceinline__ void add_overs(const GatherArgs& g, const int* tc, const int lane, const int64_t* cidx,
+                                          const int64_t lin, const bool inside)
+{
+    constexpr int NA = D + 2;
+    const MeshDev& m = g.m;
+    const R c2 = (R)g.cutoff * (R)g.cutoff;
+    double xc[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+        xc[a] = cidx[a] < m.n[a] ? cell_centre(m, a, cidx[a]) : __builtin_nan("");
+    R sum[NA];
+#pragma unroll
+    for (int k = 0; k < NA; ++k) sum[k] = 0;
+    bool hit = false;
+    for_each_run<D>(m, g.bstart, tc, lane, [&](const uint32_t s0, const uint32_t s1) {
+        for (uint32_t p0 = s0; p0 < s1; p0 += kWave) {
+            const uint32_t p = p0 + lane;
+            const int code = p < s1 ? (int)((const R*)g.rw)[(size_t)p * kRecW + kRecOver] : 0;
+            for (uint64_t bits = __ballot(code != 0); bits; bits &= bits - 1) {
+                const int e = __builtin_ctzll(bits);
+                const int c = __builtin_amdgcn_readlane(code, e);
+                const double4 P = g.rpos[p0 + e];
+                const double x[3] = {P.x, P.y, P.z};
+                const bool delta = MODE == FLA_DEPOSIT && P.w < 0.0;
+                R s = 0, ev = 1;
+#pragma unroll
+                for (int a = 0; a < D; ++a) {
+                    R sa = (R)scaled_sq(axis_offset(m, a, xc[a], x[a]), P.w), ea = gauss_factor(sa);
+                    if (delta) {
+                        const bool home = cidx[a] == home_index(m, a, x[a]);
+                        sa = home ? (R)0 : r_inf<R>();
+                        ea = (R)1;
+                    }
+                    s = a ? s + sa : sa;
+                    ev *= ea;
+                }
+                if (s <= c2) {
+                    hit = true;
+#pragma unroll
+                    for (int k = 0; k < NA; ++k)
+                        if ((c >> (2 * k)) & 3) sum[k] += ev * over_weight<R>(c, k);
+                }
+            }
+        }
+    });
+    if (!hit || !inside) return;
+    const double f = -g.scale * (g.cell_scale ? (double)((const R*)g.cell_scale)[lin] : 1.0);
+    const bool over_den = sum[0] != (R)0;          // also where it is NaN
+    const double den = over_den ? (double)sum[0] : 1.0;
+#pragma unroll
+    for (int k = 0; k <= D; ++k) {
+        const double q = (double)sum[1 + k];
+        if (q == 0.0 && !over_den) continue;
+        ((R*)g.out[k])[lin] = (R)(MODE != FLA_DEPOSIT ? (den > 0.0 ? f * (q / den) : 0.0) : f * q / m.vol);
+    }
+    if (over_den && g.den) ((R*)g.den)[lin] = sum[0];
+}
+
 // ---------------------------------------------------------------------------
 // Binary32, 3-D: whole planes of a tile per wave.
 // ---------------------------------------------------------------------------
@@ -504,7 +567,7 @@ __device__ __forceinline__ bool near_tile(const MeshDev& m, const double4 P, con
 // select and two products per pair (half tiles, three waves per SIMD): 2M
 // trajectories on 128^3 cells 4.79 -> 3.75 ms (24.8 TFLOP/s of the 15 flops
 // per included pair), 32.8M on 256^3 279.6 -> 203 ms (39 TFLOP/s).
-template <int MODE, bool COUNT, int PLAN>
+template <int MODE, bool COUNT, int PLAN, bool OVERS>
 __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile, const int share, const int shares)
 {
     using L = PlaneLds;
@@ -926,6 +989,13 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
             if (g.den) ((float*)g.den)[lin] = (float)sum[0];
         }
     }
+    if (OVERS && g.stats[ST_OVER])
+        for (int z = wave; z < ZP; z += W) {
+            const int64_t ci[3] = {cx, cy, (int64_t)tc[2] * TE + z};
+            if (!(own >> (z / 2) & 1)) continue;
+            add_overs<float, 3, MODE>(g, tc, lane, ci, cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * ci[2]),
+                                      in_xy && ci[2] < m.n[2]);
+        }
     if (COUNT) {
         // every wave holds counts for all of the workgroup's cells; integer
         // sums do not depend on the order of the atomic additions
@@ -946,7 +1016,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
 
 // The work of one workgroup: the sub-blocks of its share (every one
 // where `shares` is 1) of part `work % TP` of tile `work / TP` of the mesh of g.
-template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
+template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP, bool OVERS>
 __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work, const int share, const int shares)
 {
     constexpr int kGatherWaves = GatherWaves<R, D>::value;
@@ -1248,9 +1318,9 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
     __syncthreads();
 
     // linear index of the lane's cell in sub-block b; false beyond the mesh
-    auto cell_of = [&](int b, int64_t& lin) {
-        int64_t cidx[3] = {0, 0, 0};
+    auto cell_of = [&](int b, int64_t* cidx, int64_t& lin) {
         bool inside = true;
+        cidx[2] = 0;
 #pragma unroll
         for (int a = 0; a < D; ++a) {
             int half;
@@ -1267,8 +1337,8 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
 
     // ---- epilogue: divide (NW) or scale by 1/V_c (deposition), sign, scale
     for (int b = wave; b < NSB; b += kGatherWaves) {
-        int64_t lin;
-        if (!(own >> b & 1) || !cell_of(b, lin)) continue;
+        int64_t lin, ci[3];
+        if (!(own >> b & 1) || !cell_of(b, ci, lin)) continue;
         double tot[NA];
 #pragma unroll
         for (int k = 0; k < NA; ++k) {
@@ -1290,6 +1360,13 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
         }
         if (g.den) ((R*)g.den)[lin] = (R)den;
     }
+    if (OVERS && g.stats[ST_OVER])
+        for (int b = wave; b < NSB; b += kGatherWaves) {
+            if (!(own >> b & 1)) continue;
+            int64_t lin, ci[3];
+            const bool inside = cell_of(b, ci, lin);
+            add_overs<R, D, MODE>(g, tc, lane, ci, lin, inside);
+        }
     if (COUNT) {
         // every wave holds counts for all of the workgroup's cells (the
         // waves split the candidates, not the cells); integer sums do not
@@ -1299,8 +1376,8 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
         for (int b = 0; b < NSB; ++b) {
             if (!(own >> b & 1)) continue;
             npairs += cntb[b];
-            int64_t lin;
-            if (g.pairs && cntb[b] && cell_of(b, lin)) atomicAdd(&g.pairs[lin], cntb[b]);
+            int64_t lin, ci[3];
+            if (g.pairs && cntb[b] && cell_of(b, ci, lin)) atomicAdd(&g.pairs[lin], cntb[b]);
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) npairs += __shfl_xor(npairs, o, kWave);
@@ -1309,15 +1386,17 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
 }
 
 // Share `share` of `shares` of work item `work`, by the body of its precision
-// and dimension.
-template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
+// and dimension.  OVERS: with the weights beyond the range of R (add_overs),
+// which k_gather leaves to a launch of its own: in it they cost 5% of the 128^3
+// case, by the registers alone.
+template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP, bool OVERS>
 __device__ __forceinline__ void gather_work(const GatherArgs& g, const int work, const int share = 0,
                                             const int shares = 1)
 {
     if constexpr (sizeof(R) == 4 && D == 3)
-        gather_planes<MODE, COUNT, PLAN>(g, work, share, shares);
+        gather_planes<MODE, COUNT, PLAN, OVERS>(g, work, share, shares);
     else
-        gather_tile<R, D, MODE, COUNT, PLAN, TP>(g, work, share, shares);
+        gather_tile<R, D, MODE, COUNT, PLAN, TP, OVERS>(g, work, share, shares);
 }
 
 // Slot b of the launch belongs to XCD b % kXcds and computes the work item
@@ -1340,7 +1419,30 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
         if (slot >= total) break;
         int w = xcd_remap(slot, total);
         w = g.order[w];
-        gather_work<R, D, MODE, COUNT, PLAN, TP>(g, w);
+        gather_work<R, D, MODE, COUNT, PLAN, TP, false>(g, w);
+    }
+}
+
+// add_overs for every tile, one workgroup each.
+template <typename R, int D, int MODE>
+static __global__ __launch_bounds__(256) void k_gather_overs(GatherArgs g)
+{
+    if (!g.stats[ST_OVER]) return;
+    constexpr int TE = Geo<D>::TE, cells = D == 3 ? TE * TE * TE : TE * TE;
+    const MeshDev& m = g.m;
+    const int tile = blockIdx.x;
+    const int tc[3] = {tile % m.nt[0], (tile / m.nt[0]) % m.nt[1], D == 3 ? tile / (m.nt[0] * m.nt[1]) : 0};
+    for (int i = threadIdx.x; i < cells; i += 256) {      // whole waves
+        const int q[3] = {i % TE, (i / TE) % TE, i / (TE * TE)};
+        int64_t ci[3] = {0, 0, 0};
+        bool inside = true;
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            ci[a] = (int64_t)tc[a] * TE + q[a];
+            inside = inside && ci[a] < m.n[a];
+        }
+        add_overs<R, D, MODE>(g, tc, threadIdx.x % kWave, ci, ci[0] + (int64_t)m.n[0] * (ci[1] + (int64_t)m.n[1] * ci[2]),
+                              inside);
     }
 }
 
@@ -1353,7 +1455,7 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
     GatherArgs g, int shares)
 {
     const int w = xcd_remap(blockIdx.x, g.m.ntiles * TP * shares);
-    gather_work<R, D, MODE, COUNT, (sizeof(R) == 4 && D == 3 ? 1 : 0), TP>(g, w / shares, w % shares, shares);
+    gather_work<R, D, MODE, COUNT, (sizeof(R) == 4 && D == 3 ? 1 : 0), TP, true>(g, w / shares, w % shares, shares);
 }
 
 // Estimated work of every tile: the number of candidate records its scan
@@ -1396,10 +1498,11 @@ static __global__ __launch_bounds__(256) void k_tile_cost(GatherArgs g)
 // results do not depend on the slot that computes it.
 constexpr int kOrderBins = 33 * 4;
 static __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict__ cost, int nunits, int zs,
-                                                     int* __restrict__ order)
+                                                     int* __restrict__ order, uint32_t* __restrict__ queue)
 {
     __shared__ uint32_t cnt[kOrderBins];
     const int x = blockIdx.x;
+    if (threadIdx.x == 0) queue[x] = 0;    // the gather's counter of this XCD
     const int q = nunits / kXcds, rem = nunits % kXcds;
     const int s0 = x * q + (x < rem ? x : rem), n = q + (x < rem ? 1 : 0);
     auto bin = [](uint32_t c) {
@@ -1473,7 +1576,7 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
             else
                 hi = mid - 1;
         }
-        gather_work<R, D, MODE, COUNT, PLAN, TP>(items[lo].g, (j - items[lo].tile_base) * TP + u % TP);
+        gather_work<R, D, MODE, COUNT, PLAN, TP, true>(items[lo].g, (j - items[lo].tile_base) * TP + u % TP);
     }
 }
 
@@ -1586,15 +1689,13 @@ static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count,
         if (launch_small<R, D, MODE, COUNT, TP>(g, s)) return hipGetLastError();
         FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
         FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP,
-                   g.order);
-        // as many workgroups as the compute units hold at once; the XCD
-        // counters start at zero (a fill kernel: the launch may be captured)
+                   g.order, g.queue);
+        // as many workgroups as the compute units hold at once
         int64_t nb = (int64_t)g.m.ntiles * TP;
         const int64_t fit = resident_workgroups<R, D, TP>(g.ncu);
         if (fit < nb) nb = fit;
-        const hipError_t e = launch_fill_u32(g.queue, kXcds, 0u, s);
-        if (e != hipSuccess) return e;
         launch_plan<R, D, MODE, COUNT, TP>(g, plan, dim3((unsigned)nb), dim3(kWave * GatherWaves<R, D>::value), s);
+        FLA_LAUNCH((k_gather_overs<R, D, MODE>), dim3((unsigned)g.m.ntiles), dim3(256), 0, s, g);
         return hipGetLastError();
     };
     auto counted = [&](auto modec) {

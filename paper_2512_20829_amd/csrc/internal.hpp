@@ -11,7 +11,8 @@ namespace flp {
 constexpr int kWave = 64;
 constexpr int kClasses = 16;         // neighbourhood classes (reach 0..14 tiles, 15 = whole axes)
 constexpr int kXcds = 8;             // XCDs per MI355X
-constexpr int kRecW = 8;             // reals per weight record: w0, wq[0..C-1], padding
+constexpr int kRecW = 8;             // reals per weight record: w0, wq[0..C-1], padding, over code
+constexpr int kRecOver = kRecW - 1;  // the record's over code (split_over)
 constexpr double kSupportMargin = 1e-5;  // relative widening of conservative support tests
 
 // Tile geometry of the gather: a tile is TE^D cells processed by one wave,
@@ -66,7 +67,7 @@ void trace_launch(const char* kernel, dim3 grid, dim3 block, size_t lds, hipStre
     } while (0)
 
 // statistics slots (device int64 array)
-enum StatSlot { ST_TRAJ = 0, ST_SKIPPED, ST_NOSUPPORT, ST_PAIRS, ST_OUTSIDE, ST_ZERO, ST_MAXCLASS, ST_N };
+enum StatSlot { ST_TRAJ = 0, ST_SKIPPED, ST_NOSUPPORT, ST_PAIRS, ST_OUTSIDE, ST_ZERO, ST_MAXCLASS, ST_OVER, ST_N };
 
 // ---------------------------------------------------------------------------
 // Exact-arithmetic helpers: binary64 operations whose rounding must not be
@@ -244,6 +245,30 @@ template <int D>
 __device__ inline void droplet_phi(double r, const double* v, const double* ug, const PhysDev& ph, double* phi)
 {
     droplet_phi_t<D, double>(r, v, ug, ph, phi);
+}
+
+// Weights beyond the range of R (a tiny |det J|) become 0 in a sorted record and
+// its over code says which they were: two bits each, 1 +inf, 2 -inf, 3 NaN.  A
+// kernel weight of 0 times an infinite channel is no 0, so the gathers sum what
+// is finite and then add the others to the cells that include the record and
+// to no other.  Returns the code.
+template <typename R>
+__device__ inline int split_over(R* w)
+{
+    int code = 0;
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+        if (!isfinite(w[k])) {
+            code |= (w[k] > (R)0 ? 1 : w[k] < (R)0 ? 2 : 3) << (2 * k);
+            w[k] = (R)0;
+        }
+    return code;
+}
+template <typename R>
+__device__ inline R over_weight(int code, int k)
+{
+    const int c = (code >> (2 * k)) & 3;
+    return c == 0 ? (R)0 : c == 1 ? (R)__builtin_inf() : c == 2 ? (R)-__builtin_inf() : (R)__builtin_nan("");
 }
 
 // Floor division for possibly negative integers.

@@ -94,9 +94,12 @@ hipError_t launch_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, ui
                                 int shift = 0);
 hipError_t launch_max_class(const uint32_t* bstart, int ntiles, unsigned long long* stats, hipStream_t s);
 
+// Records in sorted order; of the first *nvalid, the weights beyond the range of R
+// go to the over code (split_over, counted in stats[ST_OVER]).
 template <typename R>
 hipError_t launch_permute(const uint32_t* order, int64_t n, const double4* rpos_u, const R* rw_u,
-                          double4* rpos, R* rw, int copy_w, hipStream_t s);
+                          double4* rpos, R* rw, int copy_w, const uint32_t* nvalid, unsigned long long* stats,
+                          hipStream_t s);
 
 template <typename R, int D>
 hipError_t launch_deposit_norm(const MeshDev& m, const PhysDev& ph, const uint32_t* nvalid,

@@ -128,7 +128,7 @@ __global__ void k_bucket_bounds(const uint32_t* keys, int64_t n, uint32_t nb, ui
 
 template <typename R>
 __global__ void k_permute(const uint32_t* order, int64_t n, const double4* rpos_u, const R* rw_u,
-                          double4* rpos, R* rw, int copy_w)
+                          double4* rpos, R* rw, int copy_w, const uint32_t* nvalid, unsigned long long* stats)
 {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
@@ -139,8 +139,17 @@ __global__ void k_permute(const uint32_t* order, int64_t n, const double4* rpos_
         constexpr int NQ = (int)(kRecW * sizeof(R) / sizeof(uint4));
         const uint4* src = reinterpret_cast<const uint4*>(rw_u + (int64_t)i * kRecW);
         uint4* dst = reinterpret_cast<uint4*>(rw + p * kRecW);
+        alignas(16) R w[kRecW];
+        uint4* wq = reinterpret_cast<uint4*>(w);
 #pragma unroll
-        for (int k = 0; k < NQ; ++k) dst[k] = src[k];
+        for (int k = 0; k < NQ; ++k) wq[k] = src[k];
+        const int code = split_over(w);
+        if (code != 0 && p < (int64_t)*nvalid) {   // records past them hold anything
+            w[kRecOver] = (R)code;
+            atomicAdd(&stats[ST_OVER], 1ull);
+        }
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) dst[k] = wq[k];
     }
 }
 
@@ -316,18 +325,28 @@ __global__ __launch_bounds__(kWave * kNormWaves) void k_deposit_norm(MeshDev m, 
             }
 #pragma unroll
             for (int o = NL / 2; o > 0; o >>= 1) z += __shfl_xor(z, o, NL);
-            if (sl == 0) {
-                // K_ci / Z_i = E_ci / z_i with z_i = sum_c E_ci (the 1/h factors cancel)
-                uint32_t i = order[p];
+            // K_ci / Z_i = E_ci / z_i with z_i = sum_c E_ci (the 1/h factors cancel);
+            // lane k forms weight k
+            if (sl <= C) {
+                const uint32_t i = order[p];
                 R* w = rw + p * kRecW;
-                if (z > 0.0) {
-                    w[0] = (R)inv_h;
-                    for (int k = 0; k < C; ++k) w[1 + k] = (R)(qd[(int64_t)k * N + i] / z);
-                } else {
-                    w[0] = (R)0;
-                    for (int k = 0; k < C; ++k) w[1 + k] = (R)qd[(int64_t)k * N + i];
-                    rpos[p].w = -inv_h;
-                    atomicAdd(&stats[ST_ZERO], 1ull);
+                double v = z > 0.0 ? inv_h : 0.0;
+                if (sl > 0) v = qd[(int64_t)(sl - 1) * N + i] / (z > 0.0 ? z : 1.0);
+                w[sl] = (R)v;
+                const bool over = !isfinite((R)v);
+                w[sl] = over ? (R)0 : (R)v;
+                int code = 0;                  // as split_over
+                if (__any(over)) {
+                    const int mine = over ? (v > 0.0 ? 1 : v < 0.0 ? 2 : 3) << (2 * sl) : 0;
+                    for (int k = 0; k <= C; ++k) code |= __shfl(mine, k, NL);
+                    if (sl == 0 && code != 0) atomicAdd(&stats[ST_OVER], 1ull);
+                }
+                if (sl == 0) {
+                    w[kRecOver] = (R)code;
+                    if (!(z > 0.0)) {
+                        rpos[p].w = -inv_h;
+                        atomicAdd(&stats[ST_ZERO], 1ull);
+                    }
                 }
             }
         }
@@ -382,11 +401,13 @@ hipError_t launch_max_class_batch(const BatchItem* items, int nsnap, const uint3
 
 template <typename R>
 hipError_t launch_permute(const uint32_t* order, int64_t n, const double4* rpos_u, const R* rw_u,
-                          double4* rpos, R* rw, int copy_w, hipStream_t s)
+                          double4* rpos, R* rw, int copy_w, const uint32_t* nvalid, unsigned long long* stats,
+                          hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     unsigned g = (unsigned)((n + 255) / 256);
-    FLA_LAUNCH((k_permute<R>), dim3(g), dim3(256), 0, s, order, n, rpos_u, rw_u, rpos, rw, copy_w);
+    FLA_LAUNCH((k_permute<R>), dim3(g), dim3(256), 0, s, order, n, rpos_u, rw_u, rpos, rw, copy_w, nvalid,
+               stats);
     return hipGetLastError();
 }
 
@@ -430,8 +451,8 @@ FLP_INST(float, 3)
 FLP_INST(double, 2)
 FLP_INST(double, 3)
 template hipError_t launch_permute<float>(const uint32_t*, int64_t, const double4*, const float*, double4*,
-                                          float*, int, hipStream_t);
-template hipError_t launch_permute<double>(const uint32_t*, int64_t, const double4*, const double*,
-                                           double4*, double*, int, hipStream_t);
+                                          float*, int, const uint32_t*, unsigned long long*, hipStream_t);
+template hipError_t launch_permute<double>(const uint32_t*, int64_t, const double4*, const double*, double4*,
+                                           double*, int, const uint32_t*, unsigned long long*, hipStream_t);
 
 }  // namespace flp
