@@ -314,8 +314,11 @@ fla_status fla_profile_read(fla_ctx* ctx, fla_profile* out);
  *      workgroups per compute unit); not in 2-D.
  * So codes 0..7 are valid in 3-D and 0..3 in 2-D.  Under one shape every
  * plan produces the same values (up to the sign of zero); they differ only
- * in speed.  Between shapes, the values are the same as well.  Codes are kept per (dim, prec) in the
- * context; -1 restores the library default (code 1).
+ * in speed.  Between shapes, the values are the same as well.  Codes are kept
+ * per (dim, prec) in the context; -1 restores the library default (code 1).
+ * A mesh so small that all its parts run at once (on 256 compute units: in 3-D
+ * up to 512 tiles in binary32 and 256 in binary64; in 2-D up to 1024 and 256)
+ * is projected in the same way under every code.
  * Errors: INVALID_ARG for out-of-range arguments. */
 #define FLA_GATHER_PLANS 4
 #define FLA_GATHER_SHAPES 2
@@ -325,11 +328,13 @@ fla_status fla_get_plan(fla_ctx* ctx, int dim, int prec, int* gather_plan);
 
 /* Autotuner: runs fla_project_sources once per gather plan code of the
  * mesh's dimension on the given inputs (a warm-up call, then a call timed
- * with HIP events), keeps the fastest code for (mesh->dim, traj->prec) in the
+ * with HIP events; codes that name the same kernel share its time), keeps the fastest code for (mesh->dim, traj->prec) in the
  * context and, if times_ms (host, FLA_GATHER_CONFIGS values, index = code) is
  * not NULL, returns the gather time of each code (-1 for codes the
- * dimension does not have).  Synchronises the device.  out receives the
- * projection.  Errors as fla_project_sources. */
+ * dimension does not have).  On a mesh that every code projects in the same way
+ * (fla_set_plan) the calls take the larger meshes' kernels, so that what is kept
+ * for those is a choice between them.  Synchronises the device.  out receives
+ * the projection.  Errors as fla_project_sources. */
 fla_status fla_autotune(fla_ctx* ctx, const fla_mesh* mesh, const fla_trajectories* traj,
                         const fla_params* params, const fla_fields* out, void* stream,
                         double* times_ms);
@@ -568,7 +573,8 @@ fla_status fla_get_batch_plan(fla_ctx* ctx, int dim, int prec, int* gather_plan,
 
 /* Batch autotuner: runs fla_project_batch directly (no graph) for every
  * gather plan code of the dimension and every chunk in {1, 4, 16, 64} (a
- * warm-up call, then a call whose gather launch is timed with HIP events),
+ * warm-up call, then a call whose gather launch is timed with HIP events; codes
+ * that name the same kernel share its time),
  * keeps the fastest pair for (dim, prec) and, if times_ms (host,
  * FLA_GATHER_CONFIGS * FLA_BATCH_CHUNKS values, index code *
  * FLA_BATCH_CHUNKS + chunk index, -1 for codes the dimension does not have)

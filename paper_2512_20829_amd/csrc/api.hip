@@ -33,6 +33,7 @@ struct fla_ctx {
     unsigned long long* stats = nullptr;   // ST_N counters
     int plan[2][2] = {{-1, -1}, {-1, -1}};  // gather plan per (dim - 2, precision); -1 = default
     bool prof = false;
+    bool tuning = false;                    // fla_autotune: the gather that the plan codes differ in, on any mesh
     struct Rec {
         int stage;
         hipEvent_t a, b;
@@ -474,7 +475,8 @@ fla_status project_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, const 
         int plan = ctx->plan[D - 2][sizeof(R) == 8 ? 1 : 0];
         if (plan < 0) plan = kDefaultPlan;
         if (out->pairs) HIP_OK(launch_fill_u32(out->pairs, m.M, 0u, s));
-        HIP_OK((launch_gather<R, D>(g, p->mode, p->count_pairs != 0 || out->pairs != nullptr, plan, s)));
+        HIP_OK((launch_gather<R, D>(g, p->mode, p->count_pairs != 0 || out->pairs != nullptr, plan, !ctx->tuning,
+                                  s)));
     }
     return FLA_OK;
 }
@@ -1557,7 +1559,15 @@ FLA_EXPORT fla_status fla_autotune(fla_ctx* ctx, const fla_mesh* mesh, const fla
     int best_plan = saved < 0 ? kDefaultPlan : saved;
     if (times_ms)
         for (int k = 0; k < FLA_GATHER_CONFIGS; ++k) times_ms[k] = -1.0;
+    ctx->tuning = true;
+    double ms_of[FLA_GATHER_CONFIGS];
     for (int plan = 0; plan < plan_codes(mesh->dim); ++plan) {
+        const int same = same_plan_code(mesh->dim, pr == FLA_F64, plan);
+        if (same < plan) {       // the same kernel
+            ms_of[plan] = ms_of[same];
+            if (times_ms) times_ms[plan] = ms_of[plan];
+            continue;
+        }
         ctx->plan[d][pr] = plan;
         // first call warms the workspace, the second is timed
         for (int rep = 0; rep < 2; ++rep) {
@@ -1573,12 +1583,14 @@ FLA_EXPORT fla_status fla_autotune(fla_ctx* ctx, const fla_mesh* mesh, const fla
         st = fla_profile_read(ctx, &pf);
         if (st != FLA_OK) break;
         double ms = pf.launches[3] ? pf.ms[3] / (double)pf.launches[3] : 1e300;
+        ms_of[plan] = ms;
         if (times_ms) times_ms[plan] = ms;
         if (ms < best) {
             best = ms;
             best_plan = plan;
         }
     }
+    ctx->tuning = false;
     (void)fla_profile_enable(ctx, was_prof ? 1 : 0);
     if (st != FLA_OK) {
         ctx->plan[d][pr] = saved;
@@ -1751,12 +1763,19 @@ FLA_EXPORT fla_status fla_autotune_batch(fla_ctx* ctx, int nsnap, const fla_mesh
     const bool was_prof = ctx->prof;
     double best = 1e300;
     int best_plan = -1, best_chunk = -1;
+    double ms_of[FLA_GATHER_CONFIGS][FLA_BATCH_CHUNKS];
     fla_status st = FLA_OK;
     try {
         if (times_ms)
             for (int k = 0; k < FLA_GATHER_CONFIGS * FLA_BATCH_CHUNKS; ++k) times_ms[k] = -1.0;
         for (int plan = 0; plan < plan_codes(meshes[0].dim) && st == FLA_OK; ++plan)
             for (int ci = 0; ci < FLA_BATCH_CHUNKS && st == FLA_OK; ++ci) {
+                const int same = same_plan_code(meshes[0].dim, pr == FLA_F64, plan);
+                if (same < plan) {       // the same kernel
+                    ms_of[plan][ci] = ms_of[same][ci];
+                    if (times_ms) times_ms[plan * FLA_BATCH_CHUNKS + ci] = ms_of[plan][ci];
+                    continue;
+                }
                 // first call warms the workspace, the second is timed
                 st = fla_profile_enable(ctx, 0);
                 if (st == FLA_OK)
@@ -1768,6 +1787,7 @@ FLA_EXPORT fla_status fla_autotune_batch(fla_ctx* ctx, int nsnap, const fla_mesh
                 if (st == FLA_OK) st = fla_profile_read(ctx, &pf);
                 if (st != FLA_OK) break;
                 const double ms = pf.launches[3] ? pf.ms[3] / (double)pf.launches[3] : 1e300;
+                ms_of[plan][ci] = ms;
                 if (times_ms) times_ms[plan * FLA_BATCH_CHUNKS + ci] = ms;
                 if (ms < best) {
                     best = ms;

@@ -1666,9 +1666,12 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
 // planes or sub-blocks of them, so the sums keep their order and their bits.
 // Whole calls with and without: 64^2 cells in binary64 107 -> 93 us, in
 // binary32 140 -> 111; 32^3 in binary32 with 100k trajectories 391 -> 343.
-template <typename R, int D, int MODE, bool COUNT, int TP>
+// A share skips as finely as there is, and shape 0 has the most workgroups, so
+// plan codes make no difference here.
+template <typename R, int D, int MODE, bool COUNT>
 static bool launch_small(const GatherArgs& g, hipStream_t s)
 {
+    constexpr int TP = tile_parts<R>(D, 0);
     constexpr int NSB = sizeof(R) == 4 && D == 3 ? 4 : Geo<D>::NSB / TP, most = NSB < 4 ? NSB : 4;
     const int64_t fit = resident_workgroups<R, D, TP>(g.ncu), parts = (int64_t)g.m.ntiles * TP;
     if (parts > fit) return false;
@@ -1680,13 +1683,13 @@ static bool launch_small(const GatherArgs& g, hipStream_t s)
 }
 
 template <typename R, int D, int TP>
-static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, hipStream_t s)
+static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, bool small, hipStream_t s)
 {
     const bool general = g.m.edges[0] || g.m.edges[1] || g.m.edges[2];
     auto launch = [&](auto modec, auto countc) -> hipError_t {
         constexpr int MODE = decltype(modec)::value;
         constexpr bool COUNT = decltype(countc)::value;
-        if (launch_small<R, D, MODE, COUNT, TP>(g, s)) return hipGetLastError();
+        if (small && launch_small<R, D, MODE, COUNT>(g, s)) return hipGetLastError();
         FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
         FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP,
                    g.order, g.queue);
@@ -1706,13 +1709,13 @@ static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count,
 }
 
 template <typename R, int D>
-hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, hipStream_t s)
+hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, bool small, hipStream_t s)
 {
     if (g.m.ntiles <= 0) return hipSuccess;
     const int plan = plan_code % kGatherPlans, shape = plan_code / kGatherPlans;
     // in 2-D there is no other shape than the first
-    if (D == 2 || shape == 0) return launch_gather_shape<R, D, tile_parts<R>(D, 0)>(g, mode, count, plan, s);
-    return launch_gather_shape<R, D, tile_parts<R>(D, D == 3)>(g, mode, count, plan, s);
+    if (D == 2 || shape == 0) return launch_gather_shape<R, D, tile_parts<R>(D, 0)>(g, mode, count, plan, small, s);
+    return launch_gather_shape<R, D, tile_parts<R>(D, D == 3)>(g, mode, count, plan, small, s);
 }
 
 }  // namespace flp

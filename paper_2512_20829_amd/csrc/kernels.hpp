@@ -113,8 +113,20 @@ hipError_t launch_deposit_norm(const MeshDev& m, const PhysDev& ph, const uint32
 constexpr int kGatherPlans = 4;
 constexpr int kGatherShapes = 2;
 template <int D> constexpr int gather_plan_codes() { return D == 3 ? kGatherPlans * kGatherShapes : kGatherPlans; }
+// Least code that is the same kernel as `code`: 2-D plans skip a sub-block or the
+// whole part; binary32 3-D has one shape and two planes as its finest skip; a
+// half tile in binary64 has four sub-blocks.
+constexpr int same_plan_code(int dim, bool f64, int code)
+{
+    const int plan = code % kGatherPlans, shape = code / kGatherPlans;
+    if (dim == 2) return plan == 0 ? 0 : 1;
+    if (!f64) return plan <= 1 ? 0 : plan;
+    return shape == 0 && plan == 3 ? 2 : code;
+}
+// small: a mesh whose parts all have a workgroup at once may take the launch that
+// no plan code changes
 template <typename R, int D>
-hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, hipStream_t s);
+hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, bool small, hipStream_t s);
 
 // PSI-CELL
 struct PsiArgs {
