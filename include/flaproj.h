@@ -317,8 +317,9 @@ fla_status fla_profile_read(fla_ctx* ctx, fla_profile* out);
  * in speed.  Between shapes, the values are the same as well.  Codes are kept
  * per (dim, prec) in the context; -1 restores the library default (code 1).
  * A mesh so small that all its parts run at once (on 256 compute units: in 3-D
- * up to 512 tiles in binary32 and 256 in binary64; in 2-D up to 1024 and 256)
- * is projected in the same way under every code.
+ * up to 512 tiles in binary32 and 256 in binary64; in 2-D up to 1024 and 256),
+ * and a binary32 3-D mesh or batch of up to 768 tiles with 1280 or more
+ * trajectories to a tile, is projected in the same way under every code.
  * Errors: INVALID_ARG for out-of-range arguments. */
 #define FLA_GATHER_PLANS 4
 #define FLA_GATHER_SHAPES 2

@@ -33,7 +33,7 @@ struct fla_ctx {
     unsigned long long* stats = nullptr;   // ST_N counters
     int plan[2][2] = {{-1, -1}, {-1, -1}};  // gather plan per (dim - 2, precision); -1 = default
     bool prof = false;
-    bool tuning = false;                    // fla_autotune: the gather that the plan codes differ in, on any mesh
+    bool tuning = false;                    // the tuners: the gathers that the plan codes differ in, on any mesh
     struct Rec {
         int stage;
         hipEvent_t a, b;
@@ -418,8 +418,7 @@ fla_status project_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, const 
            &queue);
 
     PhysDev ph{p->rho_d, p->mu, p->delta, p->h0, p->cutoff, p->scale};
-    HIP_OK(launch_fill_u64(ctx->stats, ST_N, 0ull, s));
-    HIP_OK(launch_fill_u64(ctx->stats + ST_TRAJ, 1, (unsigned long long)N, s));
+    HIP_OK(launch_init_stats(ctx->stats, N, s));
     {
         StageTimer tm(ctx, 0, s);
         if (prod)
@@ -475,8 +474,10 @@ fla_status project_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, const 
         int plan = ctx->plan[D - 2][sizeof(R) == 8 ? 1 : 0];
         if (plan < 0) plan = kDefaultPlan;
         if (out->pairs) HIP_OK(launch_fill_u32(out->pairs, m.M, 0u, s));
-        HIP_OK((launch_gather<R, D>(g, p->mode, p->count_pairs != 0 || out->pairs != nullptr, plan, !ctx->tuning,
-                                  s)));
+        static_assert(kRecW * sizeof(R) >= sizeof(double4), "weight records hold a double4");
+        const GatherSpare spare{(double*)rpos_u, (double*)rw_u, N};
+        HIP_OK((launch_gather<R, D>(g, p->mode, p->count_pairs != 0 || out->pairs != nullptr, plan,
+                                    ctx->tuning ? nullptr : &spare, s)));
     }
     return FLA_OK;
 }
@@ -547,6 +548,26 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
     const int key_bits = bits_for(nb);
     int ncu = 0;
     HIP_OK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    // Snapshots whose tiles have four workgroups each: those one of whose tiles alone
+    // takes a large part of a compute unit's share of the batch (0.4 where the batch
+    // is small, else 0.8, since the others then wait for their launch), and all where
+    // there are few tiles and many records; as far as the sums fit into the spare
+    // records.  36^3 cells with 2M trajectories beside 54^3 with 12k: 1960 -> 940 us;
+    // 34^3 with 1.8M beside 65^3 with as many 3115 -> 2374; but 36^3 with 1.2M beside
+    // 112^3 with 570k, at 0.72, would go from 2349 to 2590.
+    int64_t nsplit = 0;
+    if (sizeof(R) == 4 && D == 3 && !ctx->tuning) {
+        double work = 0.0;
+        for (int i = 0; i < nsnap; ++i) work += cost[i] * md[i].ntiles;
+        const double part = nwork <= 4 * (int64_t)ncu ? 0.4 : 0.8;
+        if (nwork <= 3 * (int64_t)ncu && total >= kSplitRecords * nwork) nsplit = nwork;
+        for (int j = 0; j < nsnap && nsplit < nwork; ++j) {
+            const int i = order[j];
+            if (cost[i] * ncu <= part * work || td[i].count < kSplitRecords * md[i].ntiles) break;
+            if (kSplitRecords * (nsplit + md[i].ntiles) > total) break;
+            nsplit += md[i].ntiles;
+        }
+    }
     const int64_t hist_w = radix_hist_words(total);
     const int64_t scan_w = scan_tmp_words(hist_w > (int64_t)nb + 1 ? hist_w : (int64_t)nb + 1);
     const int64_t n1 = total > 0 ? total : 1;
@@ -602,7 +623,7 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
         const unsigned char* b = (const unsigned char*)p;
         key.insert(key.end(), b, b + n);
     };
-    const int shape[6] = {nsnap, D, (int)sizeof(R), plan, chunk, count ? 1 : 0};
+    const int shape[7] = {nsnap, D, (int)sizeof(R), plan, chunk, count ? 1 : 0, (int)nsplit};
     put(shape, sizeof(shape));
     put(&s, sizeof(s));
     put(items.data(), sizeof(BatchItem) * nsnap);
@@ -638,8 +659,7 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
     const uint32_t sentinel = nb;
 
     auto enqueue = [&](hipStream_t q) -> fla_status {
-        HIP_OK(launch_fill_u64(ctx->stats, ST_N, 0ull, q));
-        HIP_OK(launch_fill_u64(ctx->stats + ST_TRAJ, 1, (unsigned long long)total, q));
+        HIP_OK(launch_init_stats(ctx->stats, total, q));
         {
             StageTimer tm(ctx, 0, q);
             HIP_OK((launch_prepass_batch<R, D>(dev_items, nsnap, total, sentinel, keys, vals, rpos_u, rw_u, ctx->stats,
@@ -663,8 +683,9 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
             bool general = false;     // any rectilinear axis in the batch
             for (int i = 0; i < nsnap; ++i)
                 for (int a = 0; a < 3; ++a) general = general || md[i].edges[a] != nullptr;
-            HIP_OK((launch_gather_batch<R, D>(dev_items, nsnap, (int)nwork, chunk, count, plan, general, queue,
-                                              ncu, q)));
+            const GatherSpare spare{(double*)rpos_u, (double*)rw_u, total};
+            HIP_OK((launch_gather_batch<R, D>(dev_items, nsnap, (int)nwork, (int)nsplit, chunk, count, plan, general, queue,
+                                              ncu, spare, q)));
         }
         return FLA_OK;
     };
@@ -777,8 +798,7 @@ fla_status psicell_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, double
     Carver c(ctx->ws);
     layout(c);
     a.scan_words = sw;
-    HIP_OK(launch_fill_u64(ctx->stats, ST_N, 0ull, s));
-    HIP_OK(launch_fill_u64(ctx->stats + ST_TRAJ, 1, (unsigned long long)t.count, s));
+    HIP_OK(launch_init_stats(ctx->stats, t.count, s));
     a.m = m;
     a.p = t;
     a.ph = PhysDev{p->rho_d, p->mu, p->delta, p->h0, p->cutoff, p->scale};
@@ -862,8 +882,7 @@ fla_status cic_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, double wei
     Carver c(ctx->ws);
     layout(c);
     a.scan_words = sw;
-    HIP_OK(launch_fill_u64(ctx->stats, ST_N, 0ull, s));
-    HIP_OK(launch_fill_u64(ctx->stats + ST_TRAJ, 1, (unsigned long long)t.count, s));
+    HIP_OK(launch_init_stats(ctx->stats, t.count, s));
     a.m = m;
     a.p = t;
     a.ph = PhysDev{p->rho_d, p->mu, p->delta, p->h0, p->cutoff, p->scale};
@@ -1765,6 +1784,7 @@ FLA_EXPORT fla_status fla_autotune_batch(fla_ctx* ctx, int nsnap, const fla_mesh
     int best_plan = -1, best_chunk = -1;
     double ms_of[FLA_GATHER_CONFIGS][FLA_BATCH_CHUNKS];
     fla_status st = FLA_OK;
+    ctx->tuning = true;
     try {
         if (times_ms)
             for (int k = 0; k < FLA_GATHER_CONFIGS * FLA_BATCH_CHUNKS; ++k) times_ms[k] = -1.0;
@@ -1799,6 +1819,7 @@ FLA_EXPORT fla_status fla_autotune_batch(fla_ctx* ctx, int nsnap, const fla_mesh
         ctx->err = "internal error";
         st = FLA_ERR_DEVICE;
     }
+    ctx->tuning = false;
     const std::string err = ctx->err;
     (void)fla_profile_enable(ctx, was_prof ? 1 : 0);
     ctx->err = err;
@@ -2223,8 +2244,7 @@ fla_status project_cells_impl(fla_ctx* ctx, const fla_cell_index* ix, const Traj
     Carver c(ctx->ws);
     layout(c);
     PhysDev ph{p->rho_d, p->mu, p->delta, p->h0, p->cutoff, p->scale};
-    HIP_OK(launch_fill_u64(ctx->stats, ST_N, 0ull, s));
-    HIP_OK(launch_fill_u64(ctx->stats + ST_TRAJ, 1, (unsigned long long)N, s));
+    HIP_OK(launch_init_stats(ctx->stats, N, s));
     {
         StageTimer tm(ctx, 0, s);
         HIP_OK((launch_cells_prepass<R, D>(t, ix->g, ph, p->h_factor, keys, vals, rpos_u, rw_u, ctx->stats, s)));

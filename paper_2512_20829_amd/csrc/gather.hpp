@@ -482,6 +482,19 @@ struct PlaneLds {
     float wb[NB + kWave];                  // and q_3/h
 };
 
+struct PlaneWavesLds {
+    PlaneLds w[GatherWaves<float, 3>::value];
+};
+// of a workgroup whose waves work on the same batches (SPLIT)
+struct PlaneSplitLds {
+    static constexpr int W = GatherWaves<float, 3>::value, N = 2 * W * kWave;
+    PlaneGroup grp[W][PlaneLds::NB / kPlaneRecs + 1];
+    double4 pos[N];                        // candidates of all waves
+    float4 wa[N];
+    float wb[N];
+    int cnt[W], more[W];
+};
+
 // Home-tile rows of the classes of a tile, in the order they are visited
 // (class by class, row by row, the runs of a row in x order), as one sequence
 // of runs of sorted records.
@@ -551,6 +564,21 @@ __device__ __forceinline__ bool near_tile(const MeshDev& m, const double4 P, con
     return acc <= filt2;
 }
 
+// The fields of cell lin from its sums: divided (NW) or scaled by 1/V_c
+// (deposition), sign, scale.
+template <int MODE>
+__device__ __forceinline__ void write_cell(const GatherArgs& g, const int64_t lin, const double* sum)
+{
+    const double f = -g.scale * (g.cell_scale ? (double)((const float*)g.cell_scale)[lin] : 1.0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double val = MODE != FLA_DEPOSIT ? (sum[0] > 0.0 ? f * (sum[1 + k] / sum[0]) : 0.0)
+                                               : f * sum[1 + k] / g.m.vol;
+        ((float*)g.out[k])[lin] = (float)val;
+    }
+    if (g.den) ((float*)g.den)[lin] = (float)sum[0];
+}
+
 // The work of one workgroup in binary32 and 3-D: the planes of `own` (a bit
 // per two) of one tile.  The four waves
 // take the chunks of 64 candidates in turn and keep their own sums.
@@ -567,24 +595,29 @@ __device__ __forceinline__ bool near_tile(const MeshDev& m, const double4 P, con
 // select and two products per pair (half tiles, three waves per SIMD): 2M
 // trajectories on 128^3 cells 4.79 -> 3.75 ms (24.8 TFLOP/s of the 15 flops
 // per included pair), 32.8M on 256^3 279.6 -> 203 ms (39 TFLOP/s).
-template <int MODE, bool COUNT, int PLAN, bool OVERS>
-__device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile, const int share, const int shares)
+//
+// SPLIT: the workgroup takes the chunks of one of those four waves, number
+// `share`, and writes its sums of the tile to `part` (k_split_sum adds them).  Its
+// waves scan that one's chunks together and sum 64 candidates each, and the sums of
+// every 64 are added in the candidates' order: bit for bit those of the one wave.
+template <int MODE, bool COUNT, int PLAN, bool OVERS, bool SPLIT>
+__device__ __forceinline__ void gather_planes(const GatherArgs& g, const int tile, const int share, const int shares,
+                                              double* part)
 {
     using L = PlaneLds;
     constexpr int W = GatherWaves<float, 3>::value, TE = Geo<3>::TE, ZP = TE, C = 4, NA = 5;
     constexpr int NB = L::NB, HZ = ZP / 2, GR = kPlaneRecs;
     constexpr bool kGeneral = MODE == kNwGeneral;
     static_assert(GR * ZP == 16, "one row of lanes per group");
-    const uint32_t own = ((1u << (ZP / 2 / shares)) - 1u) << (share * (ZP / 2 / shares));
     static_assert(sizeof(L) * W >= sizeof(double) * W * 4 * NA * kWave, "four planes of sums must fit");
-    __shared__ L lds[W];
+    __shared__ std::conditional_t<SPLIT, PlaneSplitLds, PlaneWavesLds> lds;
     __shared__ RunTable runs;
     __shared__ double xcs[3][TE];
 
     const MeshDev& m = g.m;
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    L& my = lds[wave];
+    const uint32_t own = SPLIT ? (1u << (ZP / 2)) - 1u : ((1u << (ZP / 2 / shares)) - 1u) << (share * (ZP / 2 / shares));
     int tc[3];
     tc[0] = tile % m.nt[0];
     tc[1] = (tile / m.nt[0]) % m.nt[1];
@@ -655,6 +688,8 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
     F4 acc[ZP];
     float den[ZP];
     double tot[ZP][NA];
+    double ptot[2][NA] = {};               // SPLIT: of planes wave and wave + W
+    static_assert(ZP == 2 * W, "two planes a wave");
     uint32_t cnt[ZP];
 #pragma unroll
     for (int z = 0; z < ZP; ++z) {
@@ -679,16 +714,15 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
     // ---- one batch of n <= NB candidates of this wave.  Lanes e and e + 32
     // stage record e: the lower half takes x and the first half of the planes,
     // the upper half y and the others (12 positions each).
-    auto process = [&](int n) {
-        wave_sync();
+    auto stage = [&](PlaneGroup* grp, const double4* pos, const float4* was, const float* wbs, int n, uint32_t* reach) {
         const int e = lane & (NB - 1), half = lane / NB;
-        PlaneGroup& gp = my.grp[e / GR];
+        PlaneGroup& gp = grp[e / GR];
         const int er = e % GR;
         // least s B of the lane's 8 positions along x or y, largest threshold
         // of its planes by twos
         float smin = r_inf<float>(), thi[2] = {-3.0e38f, -3.0e38f};
         if (e < n) {
-            const double4 P = my.pos[e];
+            const double4 P = pos[e];
             const bool delta = MODE == FLA_DEPOSIT && P.w < 0.0;
             const double hb = ldexp(delta ? -P.w : P.w, bexp / 2);
             // np positions of axis a from position p0 on: s B and e
@@ -739,7 +773,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
 #pragma unroll
             for (int q = 0; q < TE; q += 2) row[q / 2] = make_float4(sv[q], ev[q], sv[q + 1], ev[q + 1]);
             axis(2, P.z, half * HZ, bmid[2], 1.001 * bhalf[2], std::integral_constant<int, HZ>{}, sv, ev);
-            const float4 wa = my.wa[e];
+            const float4 wa = was[e];
             float tv[HZ];
 #pragma unroll
             for (int q = 0; q < HZ; ++q) {
@@ -755,7 +789,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
             td[0] = make_float4(tv[0], wa.x * ev[0], tv[1], wa.x * ev[1]);
             td[1] = make_float4(tv[2], wa.x * ev[2], tv[3], wa.x * ev[3]);
             *(float4*)&gp.ez[er][half * HZ] = make_float4(ev[0], ev[1], ev[2], ev[3]);
-            if (half) *(float4*)gp.q[er] = make_float4(wa.y, wa.z, wa.w, my.wb[e]);
+            if (half) *(float4*)gp.q[er] = make_float4(wa.y, wa.z, wa.w, wbs[e]);
         } else if (e < (n + GR - 1) / GR * GR) {
             // slots that fill up the last group reach nothing
             const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f), none = make_float4(-3.0e38f, 0.f, -3.0e38f, 0.f);
@@ -771,7 +805,6 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
         // records that reach planes 2 h and 2 h + 1 (sums of the least terms: no
         // pair is missed), one bit each; lower lanes hold h = 0, 1, upper ones
         // h = 2, 3
-        uint32_t reach[ZP / 2];
         {
             const auto mn = __builtin_amdgcn_permlane32_swap(__float_as_uint(smin), __float_as_uint(smin), false, false);
             const float mxy = __uint_as_float(mn[0]) + __uint_as_float(mn[1]);
@@ -781,10 +814,12 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
                 reach[q] = (uint32_t)any;
                 reach[q + 2] = (uint32_t)(any >> 32);
             }
-#pragma unroll
-            for (int h = 0; h < ZP / 2; ++h) reach[h] = own >> h & 1 ? reach[h] : 0u;
         }
-        wave_sync();
+    };
+    // ---- sums the n records of staged groups over the planes of `own`
+    auto evaluate = [&](const PlaneGroup* grp, int n, uint32_t* reach) {
+#pragma unroll
+        for (int h = 0; h < ZP / 2; ++h) reach[h] = own >> h & 1 ? reach[h] : 0u;
         // the next group's words are read while the current group is summed
         struct Words {
             float2 td, fx[GR], fy[GR];
@@ -802,13 +837,13 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
         };
         constexpr int UG = 4;              // groups per step of the loop
         Words w, nx;
-        load(my.grp[0], nx);
+        load(grp[0], nx);
 #pragma unroll 1
         for (int g0 = 0; g0 * GR < n; g0 += UG) {
             static_for<0, UG>([&](auto gc) {
                 constexpr int u = decltype(gc)::value;
                 w = nx;
-                load(my.grp[g0 + u + 1], nx);   // past the last group: words that are not used
+                load(grp[g0 + u + 1], nx);   // past the last group: words that are not used
                 const float tz = w.td.x, dz = w.td.y, aw = w.ez * w.q;
                 float sxy[GR], exy[GR];
 #pragma unroll
@@ -853,11 +888,11 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
 #pragma unroll
             for (int h = 0; h < ZP / 2; ++h) reach[h] >>= GR * UG;
         }
-        wave_sync();
     };
 
     // ---- scan.  Lane l holds run l of the current 64 runs: records s0 to s1
-    // and its first chunk; chunk c, c + W, ... are this wave's.
+    // and its first chunk; chunk c, c + CS, ... are this wave's.
+    constexpr int CS = SPLIT ? W * W : W;
     const int nrun = runs.base[kClasses];
     auto run_of = [&](int f, uint32_t& a0, uint32_t& a1) {
         a0 = a1 = 0;
@@ -873,7 +908,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
     };
     uint32_t s0 = 0, s1 = 0, first = 0, s0n, s1n;
     int f0 = 0;
-    uint32_t c = (uint32_t)wave, nchunk = 0;
+    uint32_t c = SPLIT ? (uint32_t)(share + W * wave) : (uint32_t)wave, nchunk = 0;
     run_of(lane, s0n, s1n);
     double4 Pn = make_double4(0, 0, 0, 0);
     float4 wan = make_float4(0, 0, 0, 0);
@@ -912,7 +947,7 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
             const int j = __popcll(__ballot(first <= c)) - 1;
             const uint32_t p = __builtin_amdgcn_readlane(s0, j) + (c - __builtin_amdgcn_readlane(first, j)) * kWave + lane;
             okn = p < __builtin_amdgcn_readlane(s1, j);
-            c += W;
+            c += CS;
             if (okn) {
                 Pn = g.rpos[p];
                 const float* w = (const float*)g.rw + (size_t)p * kRecW;
@@ -922,71 +957,148 @@ __device__ __forceinline__ void gather_planes(const GatherArgs& g, const int til
         }
         const bool ok = inr && near_tile<MODE == FLA_DEPOSIT>(m, P, tc, bmid, bhalf, faxis, g.filt2);
         const uint64_t bal = __ballot(ok);
-        if (ok) {
-            const int at = ncand + __popcll(bal & ltmask);
-            my.pos[at] = P;
-            my.wa[at] = wa;
-            my.wb[at] = wb;
-        }
-        ncand += __popcll(bal);
-        while (ncand >= (more ? NB : 1)) {
-            const int n = ncand < NB ? ncand : NB;
-            process(n);
-            // binary32 partial sums run over at most 64 records
-            if (++nfold == kWave / NB) {
-                fold();
-                nfold = 0;
+        if constexpr (SPLIT) {
+            // the waves' candidates in the order of their chunks
+            if (lane == 0) {
+                lds.cnt[wave] = __popcll(bal);
+                lds.more[wave] = more;
             }
-            const int rem = ncand - n;
-            if (rem > 0) {
-                const int at = n + (lane < rem ? lane : 0);
-                const double4 mp = my.pos[at];
-                const float4 ma = my.wa[at];
-                const float mb = my.wb[at];
-                wave_sync();
-                if (lane < rem) {
-                    my.pos[lane] = mp;
-                    my.wa[lane] = ma;
-                    my.wb[lane] = mb;
+            __syncthreads();
+            int at = ncand + __popcll(bal & ltmask);
+            more = false;
+#pragma unroll
+            for (int t = 0; t < W; ++t) {
+                const int ct = __builtin_amdgcn_readfirstlane(lds.cnt[t]);
+                at += t < wave ? ct : 0;
+                ncand += ct;
+                more = more || __builtin_amdgcn_readfirstlane(lds.more[t]) != 0;
+            }
+            if (ok) {
+                lds.pos[at] = P;
+                lds.wa[at] = wa;
+                lds.wb[at] = wb;
+            }
+            __syncthreads();
+            while (ncand >= (more ? W * kWave : 1)) {
+                // each wave sums 64 records over all planes, as one wave sums them
+                // between two folds
+                const int n = ncand < W * kWave ? ncand : W * kWave;
+#pragma unroll 1
+                for (int o = wave * kWave; o < (wave + 1) * kWave && o < n; o += NB) {
+                    const int nu = n - o < NB ? n - o : NB;
+                    uint32_t reach[ZP / 2];
+                    wave_sync();
+                    stage(lds.grp[wave], lds.pos + o, lds.wa + o, lds.wb + o, nu, reach);
+                    wave_sync();
+                    evaluate(lds.grp[wave], nu, reach);
                 }
+                // their sums, in the order of the records, to those of planes wave
+                // and wave + 4
+                float* ex = reinterpret_cast<float*>(lds.grp);   // [wave][plane][k][lane]
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    __syncthreads();
+#pragma unroll
+                    for (int u = 0; u < W; ++u) {
+                        float* e = ex + (wave * W + u) * NA * kWave + lane;
+                        e[0] = den[W * h + u];
+#pragma unroll
+                        for (int k = 0; k < C; ++k) e[(1 + k) * kWave] = acc[W * h + u][k];
+                        den[W * h + u] = 0.f;
+                        acc[W * h + u] = F4{0.f, 0.f, 0.f, 0.f};
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int v = 0; v < W; ++v)
+#pragma unroll
+                        for (int k = 0; k < NA; ++k)
+                            ptot[h][k] += (double)ex[((v * W + wave) * NA + k) * kWave + lane];
+                }
+                const int rem = ncand - n, tid = threadIdx.x, from = n + (tid < rem ? tid : 0);
+                const double4 mp = lds.pos[from];
+                const float4 ma = lds.wa[from];
+                const float mb = lds.wb[from];
+                __syncthreads();
+                if (tid < rem) {
+                    lds.pos[tid] = mp;
+                    lds.wa[tid] = ma;
+                    lds.wb[tid] = mb;
+                }
+                __syncthreads();
+                ncand = rem;
             }
-            ncand = rem;
+        } else {
+            L& my = lds.w[wave];
+            if (ok) {
+                const int at = ncand + __popcll(bal & ltmask);
+                my.pos[at] = P;
+                my.wa[at] = wa;
+                my.wb[at] = wb;
+            }
+            ncand += __popcll(bal);
+            while (ncand >= (more ? NB : 1)) {
+                const int n = ncand < NB ? ncand : NB;
+                uint32_t reach[ZP / 2];
+                wave_sync();
+                stage(my.grp, my.pos, my.wa, my.wb, n, reach);
+                wave_sync();
+                evaluate(my.grp, n, reach);
+                wave_sync();
+                // binary32 partial sums run over at most 64 records
+                if (++nfold == kWave / NB) {
+                    fold();
+                    nfold = 0;
+                }
+                const int rem = ncand - n;
+                if (rem > 0) {
+                    const int at = n + (lane < rem ? lane : 0);
+                    const double4 mp = my.pos[at];
+                    const float4 ma = my.wa[at];
+                    const float mb = my.wb[at];
+                    wave_sync();
+                    if (lane < rem) {
+                        my.pos[lane] = mp;
+                        my.wa[lane] = ma;
+                        my.wb[lane] = mb;
+                    }
+                }
+                ncand = rem;
+            }
         }
     }
-    fold();
+    if (!SPLIT) fold();
 
-    // ---- the waves' sums, four planes at a time through LDS, added in wave
-    // order; then divide (NW) or scale by 1/V_c (deposition), sign, scale
-    double* red = reinterpret_cast<double*>(lds);   // [wave][plane][k][lane]
     const int64_t cx = (int64_t)tc[0] * TE + lx, cy = (int64_t)tc[1] * TE + ly;
     const bool in_xy = cx < m.n[0] && cy < m.n[1];
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int z0 = 0; z0 < ZP; z0 += 4) {
-        __syncthreads();
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+            for (int k = 0; k < NA; ++k) part[((W * h + wave) * NA + k) * kWave + lane] = ptot[h][k];
+    } else {
+        // ---- the waves' sums, four planes at a time through LDS, added in wave
+        // order
+        double* red = reinterpret_cast<double*>(&lds);   // [wave][plane][k][lane]
 #pragma unroll
-            for (int k = 0; k < NA; ++k) red[((wave * 4 + u) * NA + k) * kWave + lane] = tot[z0 + u][k];
-        __syncthreads();
-        const int64_t cz = (int64_t)tc[2] * TE + z0 + wave;
-        if (in_xy && cz < m.n[2] && (own >> ((z0 + wave) / 2) & 1)) {
-            const int64_t lin = cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * cz);
-            double sum[NA];
+        for (int z0 = 0; z0 < ZP; z0 += 4) {
+            __syncthreads();
 #pragma unroll
-            for (int k = 0; k < NA; ++k) {
-                double a = 0.0;
+            for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int v = 0; v < W; ++v) a += red[((v * 4 + wave) * NA + k) * kWave + lane];
-                sum[k] = a;
+                for (int k = 0; k < NA; ++k) red[((wave * 4 + u) * NA + k) * kWave + lane] = tot[z0 + u][k];
+            __syncthreads();
+            const int64_t cz = (int64_t)tc[2] * TE + z0 + wave;
+            if (in_xy && cz < m.n[2] && (own >> ((z0 + wave) / 2) & 1)) {
+                double sum[NA];
+#pragma unroll
+                for (int k = 0; k < NA; ++k) {
+                    double a = 0.0;
+#pragma unroll
+                    for (int v = 0; v < W; ++v) a += red[((v * 4 + wave) * NA + k) * kWave + lane];
+                    sum[k] = a;
+                }
+                write_cell<MODE>(g, cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * cz), sum);
             }
-            const double f = -g.scale * (g.cell_scale ? (double)((const float*)g.cell_scale)[lin] : 1.0);
-#pragma unroll
-            for (int k = 0; k < C; ++k) {
-                const double val = MODE != FLA_DEPOSIT ? (sum[0] > 0.0 ? f * (sum[1 + k] / sum[0]) : 0.0)
-                                                       : f * sum[1 + k] / m.vol;
-                ((float*)g.out[k])[lin] = (float)val;
-            }
-            if (g.den) ((float*)g.den)[lin] = (float)sum[0];
         }
     }
     if (OVERS && g.stats[ST_OVER])
@@ -1387,14 +1499,15 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
 
 // Share `share` of `shares` of work item `work`, by the body of its precision
 // and dimension.  OVERS: with the weights beyond the range of R (add_overs),
-// which k_gather leaves to a launch of its own: in it they cost 5% of the 128^3
-// case, by the registers alone.
+// which the persistent gathers and gather_planes leave to a launch of their own
+// (k_gather_overs): in them they cost 5 to 13%, by the registers alone.
+template <typename R, int D> constexpr bool kPlanes = sizeof(R) == 4 && D == 3;   // gather_planes
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP, bool OVERS>
 __device__ __forceinline__ void gather_work(const GatherArgs& g, const int work, const int share = 0,
                                             const int shares = 1)
 {
-    if constexpr (sizeof(R) == 4 && D == 3)
-        gather_planes<MODE, COUNT, PLAN, OVERS>(g, work, share, shares);
+    if constexpr (kPlanes<R, D>)
+        gather_planes<MODE, COUNT, PLAN, OVERS, false>(g, work, share, shares, nullptr);
     else
         gather_tile<R, D, MODE, COUNT, PLAN, TP, OVERS>(g, work, share, shares);
 }
@@ -1425,12 +1538,10 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
 
 // add_overs for every tile, one workgroup each.
 template <typename R, int D, int MODE>
-static __global__ __launch_bounds__(256) void k_gather_overs(GatherArgs g)
+__device__ __forceinline__ void overs_tile(const GatherArgs& g, const int tile)
 {
-    if (!g.stats[ST_OVER]) return;
     constexpr int TE = Geo<D>::TE, cells = D == 3 ? TE * TE * TE : TE * TE;
     const MeshDev& m = g.m;
-    const int tile = blockIdx.x;
     const int tc[3] = {tile % m.nt[0], (tile / m.nt[0]) % m.nt[1], D == 3 ? tile / (m.nt[0] * m.nt[1]) : 0};
     for (int i = threadIdx.x; i < cells; i += 256) {      // whole waves
         const int q[3] = {i % TE, (i / TE) % TE, i / (TE * TE)};
@@ -1445,6 +1556,12 @@ static __global__ __launch_bounds__(256) void k_gather_overs(GatherArgs g)
                               inside);
     }
 }
+template <typename R, int D, int MODE>
+static __global__ __launch_bounds__(256) void k_gather_overs(GatherArgs g)
+{
+    if (!g.stats[ST_OVER]) return;
+    overs_tile<R, D, MODE>(g, blockIdx.x);
+}
 
 // Every share of every part of every tile with a workgroup of its own (small
 // meshes).  A kernel beside the one above, which pays 2% for the shares on the
@@ -1455,7 +1572,49 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
     GatherArgs g, int shares)
 {
     const int w = xcd_remap(blockIdx.x, g.m.ntiles * TP * shares);
-    gather_work<R, D, MODE, COUNT, (sizeof(R) == 4 && D == 3 ? 1 : 0), TP, true>(g, w / shares, w % shares, shares);
+    gather_work<R, D, MODE, COUNT, (sizeof(R) == 4 && D == 3 ? 1 : 0), TP, !kPlanes<R, D>>(g, w / shares, w % shares, shares);
+}
+
+// Binary32 3-D meshes of few tiles with many records each: four workgroups to a
+// tile, each with the chunks of one of the four waves that the tile would have (so
+// the sums keep their bits), and its sums in part, 20 KiB a workgroup: those of
+// waves 0 and 1 of all tiles in part01, of 2 and 3 in part23.
+constexpr int kSplitWords = 8 * 5 * kWave;
+template <int MODE, bool COUNT>
+static __global__ __launch_bounds__(256, 2) void k_gather_split(GatherArgs g, double* part01, double* part23)
+{
+    const int w = xcd_remap(blockIdx.x, g.m.ntiles * 4), tile = w / 4, v = w % 4;
+    double* part = (v < 2 ? part01 : part23) + (size_t)(tile * 2 + v % 2) * kSplitWords;
+    gather_planes<MODE, COUNT, 1, false, true>(g, tile, v, 1, part);
+}
+// The fields from those sums, added in the order of the waves: four planes of a
+// tile to a workgroup.
+template <int MODE>
+__device__ __forceinline__ void split_sum(const GatherArgs& g, const int tile, const int at, const double* part01,
+                                          const double* part23)
+{
+    constexpr int TE = Geo<3>::TE, NA = 5;
+    const MeshDev& m = g.m;
+    const int lane = threadIdx.x % kWave, z = blockIdx.x % 2 * 4 + threadIdx.x / kWave;
+    const int64_t cx = (int64_t)(tile % m.nt[0]) * TE + lane % TE;
+    const int64_t cy = (int64_t)((tile / m.nt[0]) % m.nt[1]) * TE + lane / TE;
+    const int64_t cz = (int64_t)(tile / (m.nt[0] * m.nt[1])) * TE + z;
+    if (cx >= m.n[0] || cy >= m.n[1] || cz >= m.n[2]) return;
+    double sum[NA];
+#pragma unroll
+    for (int k = 0; k < NA; ++k) {
+        double a = 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            a += ((v < 2 ? part01 : part23) + (size_t)(at * 2 + v % 2) * kSplitWords)[(z * NA + k) * kWave + lane];
+        sum[k] = a;
+    }
+    write_cell<MODE>(g, cx + (int64_t)m.n[0] * (cy + (int64_t)m.n[1] * cz), sum);
+}
+template <int MODE>
+static __global__ __launch_bounds__(256) void k_split_sum(GatherArgs g, const double* part01, const double* part23)
+{
+    split_sum<MODE>(g, blockIdx.x / 2, blockIdx.x / 2, part01, part23);
 }
 
 // Estimated work of every tile: the number of candidate records its scan
@@ -1542,8 +1701,47 @@ static __device__ inline int batch_work_item(int bid, int nwork, int chunk)
     return c * span + (off % kXcds) * chunk + off / kXcds;
 }
 
-// Persistent workgroups over the work items of a batch, one (snapshot,
-// tile part) at a time.  The snapshots are stored in work-list order:
+// Last snapshot whose first work item is <= j.
+static __device__ inline int batch_snapshot(const BatchItem* __restrict__ items, int nsnap, int j)
+{
+    int lo = 0, hi = nsnap - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (items[mid].tile_base <= j)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+template <typename R, int D, int MODE>
+static __global__ __launch_bounds__(256) void k_gather_batch_overs(const BatchItem* __restrict__ items, int nsnap)
+{
+    if (!items[0].g.stats[ST_OVER]) return;    // of the whole call
+    const int j = blockIdx.x, i = batch_snapshot(items, nsnap, j);
+    overs_tile<R, D, MODE>(items[i].g, j - items[i].tile_base);
+}
+
+// k_gather_split and k_split_sum over the tiles of a batch.
+template <int MODE, bool COUNT>
+static __global__ __launch_bounds__(256, 2) void k_gather_split_batch(const BatchItem* __restrict__ items, int nsnap,
+                                                                      double* part01, double* part23)
+{
+    const int j = blockIdx.x / 4, v = blockIdx.x % 4, i = batch_snapshot(items, nsnap, j);   // heaviest first
+    double* part = (v < 2 ? part01 : part23) + (size_t)(j * 2 + v % 2) * kSplitWords;
+    gather_planes<MODE, COUNT, 1, false, true>(items[i].g, j - items[i].tile_base, v, 1, part);
+}
+template <int MODE>
+static __global__ __launch_bounds__(256) void k_split_sum_batch(const BatchItem* __restrict__ items, int nsnap,
+                                                                const double* part01, const double* part23)
+{
+    const int j = blockIdx.x / 2, i = batch_snapshot(items, nsnap, j);
+    split_sum<MODE>(items[i].g, j - items[i].tile_base, j, part01, part23);
+}
+
+// Persistent workgroups over nwork work items of a batch from `first` on, one
+// (snapshot, tile part) at a time.  The snapshots are stored in work-list order:
 // items[s].tile_base is the first work item of snapshot s.  Slot b of the
 // ordered launch (batch_work_item) belongs to XCD b % kXcds; each XCD has
 // its own counter (queue[x], zeroed before the launch), from which its
@@ -1555,7 +1753,7 @@ static __device__ inline int batch_work_item(int bid, int nwork, int chunk)
 // its results.
 template <typename R, int D, int MODE, bool COUNT, int PLAN, int TP>
 static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherOcc<R, D, TP>::value)) void k_gather_batch(
-    const BatchItem* __restrict__ items, int nsnap, int nwork, int chunk, uint32_t* __restrict__ queue)
+    const BatchItem* __restrict__ items, int nsnap, int first, int nwork, int chunk, uint32_t* __restrict__ queue)
 {
     __shared__ int s_slot;
     const int total = nwork * TP;
@@ -1567,16 +1765,9 @@ static __global__ __launch_bounds__((kWave * GatherWaves<R, D>::value), (GatherO
         const int slot = s_slot;
         if (slot >= total) break;
         const int u = batch_work_item(slot, total, chunk);
-        const int j = u / TP;         // tile-level work item
-        int lo = 0, hi = nsnap - 1;   // last snapshot whose first work item is <= j
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (items[mid].tile_base <= j)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        gather_work<R, D, MODE, COUNT, PLAN, TP, true>(items[lo].g, (j - items[lo].tile_base) * TP + u % TP);
+        const int j = first + u / TP;         // tile-level work item
+        const int lo = batch_snapshot(items, nsnap, j);
+        gather_work<R, D, MODE, COUNT, PLAN, TP, false>(items[lo].g, (j - items[lo].tile_base) * TP + u % TP);
     }
 }
 
@@ -1605,7 +1796,7 @@ static int64_t resident_workgroups(int ncu)
 }
 
 template <typename R, int D, int MODE, bool COUNT, int TP>
-static void launch_batch_plan(const BatchItem* items, int nsnap, int nwork, int chunk, int plan, uint32_t* queue,
+static void launch_batch_plan(const BatchItem* items, int nsnap, int first, int nwork, int chunk, int plan, uint32_t* queue,
                               int ncu, hipStream_t s)
 {
     // as many workgroups as the compute units hold, at most one per item
@@ -1616,46 +1807,90 @@ static void launch_batch_plan(const BatchItem* items, int nsnap, int nwork, int 
     dim3 grid((unsigned)nb), block(kWave * GatherWaves<R, D>::value);
     constexpr int kFinest = finest_plan<R, D>();
     switch (plan) {
-    case 1: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 1, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
-    case 2: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 2, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
-    case 3: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 3, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
-    default: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, kFinest, TP>), grid, block, 0, s, items, nsnap, nwork, chunk, queue); break;
+    case 1: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 1, TP>), grid, block, 0, s, items, nsnap, first, nwork, chunk, queue); break;
+    case 2: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 2, TP>), grid, block, 0, s, items, nsnap, first, nwork, chunk, queue); break;
+    case 3: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, 3, TP>), grid, block, 0, s, items, nsnap, first, nwork, chunk, queue); break;
+    default: FLA_LAUNCH((k_gather_batch<R, D, MODE, COUNT, kFinest, TP>), grid, block, 0, s, items, nsnap, first, nwork, chunk, queue); break;
     }
 }
 
 template <typename R, int D, int TP>
-static void launch_batch_shape(const BatchItem* items, int nsnap, int nwork, int chunk, bool count, int plan,
+static void launch_batch_shape(const BatchItem* items, int nsnap, int first, int nwork, int chunk, bool count, int plan,
                                bool general, uint32_t* queue, int ncu, hipStream_t s)
 {
     if (general) {
         if (count)
-            launch_batch_plan<R, D, kNwGeneral, true, TP>(items, nsnap, nwork, chunk, plan, queue, ncu, s);
+            launch_batch_plan<R, D, kNwGeneral, true, TP>(items, nsnap, first, nwork, chunk, plan, queue, ncu, s);
         else
-            launch_batch_plan<R, D, kNwGeneral, false, TP>(items, nsnap, nwork, chunk, plan, queue, ncu, s);
+            launch_batch_plan<R, D, kNwGeneral, false, TP>(items, nsnap, first, nwork, chunk, plan, queue, ncu, s);
     } else {
         if (count)
-            launch_batch_plan<R, D, FLA_NW, true, TP>(items, nsnap, nwork, chunk, plan, queue, ncu, s);
+            launch_batch_plan<R, D, FLA_NW, true, TP>(items, nsnap, first, nwork, chunk, plan, queue, ncu, s);
         else
-            launch_batch_plan<R, D, FLA_NW, false, TP>(items, nsnap, nwork, chunk, plan, queue, ncu, s);
+            launch_batch_plan<R, D, FLA_NW, false, TP>(items, nsnap, first, nwork, chunk, plan, queue, ncu, s);
     }
 }
 
-// plan_code = plan + kGatherPlans * shape (shape 1: whole tiles, 3-D only)
+// Whether four workgroups to a tile (k_gather_split) take less time than one.  They
+// do where compute units would be left idle: up to one tile to a unit always
+// (whole calls in binary32, one workgroup or up to four that share a tile's planes,
+// against split: 20^3 cells and 1M trajectories 2477 -> 988 us, 40^3 and 1M 1010 ->
+// 525, 30^3 and 100k 342 -> 181); above, where the last units' second or third
+// tile costs more than the tenth that the exchange of the sums does (343 tiles and
+// 1M 733 -> 666, 320 tiles 744 -> 637, but 512 tiles 631 -> 694).  And only where
+// the sums, 80 KiB a tile, fit into the spare records: at fewer records a tile
+// the scan is short and there is little to share.
+static_assert(kSplitRecords * sizeof(double4) >= 2 * kSplitWords * sizeof(double), "the sums fit into the spare records");
+template <int MODE> static bool split_pays(int64_t tiles, int64_t records, int ncu)
+{
+    if (records < kSplitRecords * tiles || tiles > 3 * (int64_t)ncu) return false;
+    const int64_t whole = (tiles + ncu - 1) / ncu, quarters = (4 * tiles + ncu - 1) / ncu;
+    return whole <= 1 || (MODE == FLA_DEPOSIT ? 10 * quarters <= 40 * whole : 11 * quarters < 40 * whole);
+}
+
+template <int MODE, bool COUNT>
+static void launch_split_batch(const BatchItem* items, int nsnap, int nwork, const GatherSpare& spare, hipStream_t s)
+{
+    FLA_LAUNCH((k_gather_split_batch<MODE, COUNT>), dim3((unsigned)nwork * 4), dim3(256), 0, s, items, nsnap, spare.a,
+               spare.b);
+    FLA_LAUNCH((k_split_sum_batch<MODE>), dim3((unsigned)nwork * 2), dim3(256), 0, s, items, nsnap,
+               (const double*)spare.a, (const double*)spare.b);
+}
+
+// plan_code = plan + kGatherPlans * shape (shape 1: whole tiles, 3-D only).  The first nsplit work items, of binary32 3-D snapshots that the caller has found
+// heavy, go to four workgroups each.
 template <typename R, int D>
-hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int chunk, bool count, int plan_code,
-                               bool general, uint32_t* queue, int ncu, hipStream_t s)
+hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int nsplit, int chunk, bool count,
+                               int plan_code, bool general, uint32_t* queue, int ncu, const GatherSpare& spare,
+                               hipStream_t s)
 {
     if (nwork <= 0) return hipSuccess;
     const int plan = plan_code % kGatherPlans, shape = plan_code / kGatherPlans;
-    // the XCD counters start at zero (a fill kernel: the launch may be captured)
-    hipError_t e = launch_fill_u32(queue, kXcds, 0u, s);
-    if (e != hipSuccess) return e;
-    // in 2-D there is no other shape than the first
-    if (D == 2 || shape == 0)
-        launch_batch_shape<R, D, tile_parts<R>(D, 0)>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu, s);
-    else
-        launch_batch_shape<R, D, tile_parts<R>(D, D == 3)>(items, nsnap, nwork, chunk, count, plan, general, queue, ncu,
-                                                           s);
+    int first = 0;
+    if constexpr (kPlanes<R, D>) {
+        if (nsplit > 0) {
+            if (general)
+                count ? launch_split_batch<kNwGeneral, true>(items, nsnap, nsplit, spare, s)
+                      : launch_split_batch<kNwGeneral, false>(items, nsnap, nsplit, spare, s);
+            else
+                count ? launch_split_batch<FLA_NW, true>(items, nsnap, nsplit, spare, s)
+                      : launch_split_batch<FLA_NW, false>(items, nsnap, nsplit, spare, s);
+            first = nsplit;
+        }
+    }
+    if (first < nwork) {
+        // the XCD counters start at zero (a fill kernel: the launch may be captured)
+        hipError_t e = launch_fill_u32(queue, kXcds, 0u, s);
+        if (e != hipSuccess) return e;
+        // in 2-D there is no other shape than the first
+        if (D == 2 || shape == 0)
+            launch_batch_shape<R, D, tile_parts<R>(D, 0)>(items, nsnap, first, nwork - first, chunk, count, plan, general,
+                                                          queue, ncu, s);
+        else
+            launch_batch_shape<R, D, tile_parts<R>(D, D == 3)>(items, nsnap, first, nwork - first, chunk, count, plan,
+                                                               general, queue, ncu, s);
+    }
+    FLA_LAUNCH((k_gather_batch_overs<R, D, FLA_NW>), dim3((unsigned)nwork), dim3(256), 0, s, items, nsnap);
     return hipGetLastError();
 }
 
@@ -1679,17 +1914,29 @@ static bool launch_small(const GatherArgs& g, hipStream_t s)
     while (2 * shares <= most && parts * 2 * shares <= fit) shares *= 2;
     FLA_LAUNCH((k_gather_small<R, D, MODE, COUNT, TP>), dim3((unsigned)(parts * shares)),
                dim3(kWave * GatherWaves<R, D>::value), 0, s, g, shares);
+    if (kPlanes<R, D>) FLA_LAUNCH((k_gather_overs<R, D, MODE>), dim3((unsigned)g.m.ntiles), dim3(256), 0, s, g);
     return true;
 }
 
 template <typename R, int D, int TP>
-static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, bool small, hipStream_t s)
+static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, const GatherSpare* spare,
+                                      hipStream_t s)
 {
     const bool general = g.m.edges[0] || g.m.edges[1] || g.m.edges[2];
     auto launch = [&](auto modec, auto countc) -> hipError_t {
         constexpr int MODE = decltype(modec)::value;
         constexpr bool COUNT = decltype(countc)::value;
-        if (small && launch_small<R, D, MODE, COUNT>(g, s)) return hipGetLastError();
+        if constexpr (kPlanes<R, D>) {
+            if (spare && split_pays<MODE>(g.m.ntiles, spare->records, g.ncu)) {
+                const unsigned nt = (unsigned)g.m.ntiles;
+                FLA_LAUNCH((k_gather_split<MODE, COUNT>), dim3(nt * 4), dim3(256), 0, s, g, spare->a, spare->b);
+                FLA_LAUNCH((k_split_sum<MODE>), dim3(nt * 2), dim3(256), 0, s, g, (const double*)spare->a,
+                           (const double*)spare->b);
+                FLA_LAUNCH((k_gather_overs<R, D, MODE>), dim3(nt), dim3(256), 0, s, g);
+                return hipGetLastError();
+            }
+        }
+        if (spare && launch_small<R, D, MODE, COUNT>(g, s)) return hipGetLastError();
         FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
         FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP,
                    g.order, g.queue);
@@ -1709,13 +1956,14 @@ static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count,
 }
 
 template <typename R, int D>
-hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, bool small, hipStream_t s)
+hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, const GatherSpare* spare,
+                         hipStream_t s)
 {
     if (g.m.ntiles <= 0) return hipSuccess;
     const int plan = plan_code % kGatherPlans, shape = plan_code / kGatherPlans;
     // in 2-D there is no other shape than the first
-    if (D == 2 || shape == 0) return launch_gather_shape<R, D, tile_parts<R>(D, 0)>(g, mode, count, plan, small, s);
-    return launch_gather_shape<R, D, tile_parts<R>(D, D == 3)>(g, mode, count, plan, small, s);
+    if (D == 2 || shape == 0) return launch_gather_shape<R, D, tile_parts<R>(D, 0)>(g, mode, count, plan, spare, s);
+    return launch_gather_shape<R, D, tile_parts<R>(D, D == 3)>(g, mode, count, plan, spare, s);
 }
 
 }  // namespace flp

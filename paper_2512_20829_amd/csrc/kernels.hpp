@@ -47,9 +47,18 @@ hipError_t launch_max_class_batch(const BatchItem* items, int nsnap, const uint3
                                   unsigned long long* stats, hipStream_t s);
 // Persistent gather over the work items of a batch; queue holds kXcds
 // counters of workspace (zeroed by the launcher), ncu the compute units.
+// Memory that the gather may use: the unsorted records, `records` double4 each.
+struct GatherSpare {
+    double *a, *b;
+    int64_t records;
+};
+// records a tile from which four workgroups share it (k_gather_split), and the spare
+// ones that hold their sums
+constexpr int64_t kSplitRecords = 1280;
 template <typename R, int D>
-hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int chunk, bool count, int plan_code,
-                               bool general, uint32_t* queue, int ncu, hipStream_t s);
+hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int nsplit, int chunk, bool count,
+                               int plan_code, bool general, uint32_t* queue, int ncu, const GatherSpare& spare,
+                               hipStream_t s);
 
 // Trajectory producer: the gas field and the droplet state it advances.
 struct FlowDev {
@@ -123,10 +132,11 @@ constexpr int same_plan_code(int dim, bool f64, int code)
     if (!f64) return plan <= 1 ? 0 : plan;
     return shape == 0 && plan == 3 ? 2 : code;
 }
-// small: a mesh whose parts all have a workgroup at once may take the launch that
-// no plan code changes
+// spare: a mesh whose parts all have a workgroup at once may take the launches that
+// no plan code changes; null: the one that the plan codes differ in
 template <typename R, int D>
-hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, bool small, hipStream_t s);
+hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, const GatherSpare* spare,
+                         hipStream_t s);
 
 // PSI-CELL
 struct PsiArgs {
@@ -259,6 +269,7 @@ template <typename R, int D>
 hipError_t launch_cells_gather(const CellsGatherArgs& a, bool count, hipStream_t s);
 
 hipError_t launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipStream_t s);
+hipError_t launch_init_stats(unsigned long long* stats, int64_t count, hipStream_t s);
 hipError_t launch_fill_u32(unsigned int* p, int64_t n, unsigned int v, hipStream_t s);
 template <typename R>
 hipError_t launch_fill_real(R* p, int64_t n, hipStream_t s);

@@ -1144,6 +1144,11 @@ __global__ void k_fill_u64(unsigned long long* p, int64_t n, unsigned long long 
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
 }
+// The counters of a call: its number of trajectories, the others 0.
+__global__ void k_init_stats(unsigned long long* stats, unsigned long long count)
+{
+    if (threadIdx.x < ST_N) stats[threadIdx.x] = threadIdx.x == ST_TRAJ ? count : 0ull;
+}
 __global__ void k_fill_u32(unsigned int* p, int64_t n, unsigned int v)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -1168,6 +1173,11 @@ hipError_t launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long 
 {
     if (n <= 0) return hipSuccess;
     FLA_LAUNCH(k_fill_u64, dim3(grid_for(n)), dim3(256), 0, s, p, n, v);
+    return hipGetLastError();
+}
+hipError_t launch_init_stats(unsigned long long* stats, int64_t count, hipStream_t s)
+{
+    FLA_LAUNCH(k_init_stats, dim3(1), dim3(64), 0, s, stats, (unsigned long long)count);
     return hipGetLastError();
 }
 hipError_t launch_fill_u32(unsigned int* p, int64_t n, unsigned int v, hipStream_t s)
