@@ -308,7 +308,8 @@ fla_status fla_profile_read(fla_ctx* ctx, fla_profile* out);
  * In 2-D, plans 1-3 skip only the whole tile.
  * The shape is the part of a tile (8^3 or 16^2 cells) one workgroup owns:
  *   0: in binary64 half a tile along x (4 sub-blocks in 3-D, 2 in 2-D; the
- *      default), else the whole tile;
+ *      default; in 2-D with few trajectories to a tile the whole tile), else
+ *      the whole tile;
  *   1: the whole tile in 3-D (in binary64 8 sub-blocks: the candidates are
  *      scanned and staged once per tile instead of once per half, with fewer
  *      workgroups per compute unit); not in 2-D.

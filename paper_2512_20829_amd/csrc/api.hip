@@ -475,9 +475,9 @@ fla_status project_impl(fla_ctx* ctx, const MeshDev& m, const TrajDev& t, const 
         if (plan < 0) plan = kDefaultPlan;
         if (out->pairs) HIP_OK(launch_fill_u32(out->pairs, m.M, 0u, s));
         static_assert(kRecW * sizeof(R) >= sizeof(double4), "weight records hold a double4");
-        const GatherSpare spare{(double*)rpos_u, (double*)rw_u, N};
-        HIP_OK((launch_gather<R, D>(g, p->mode, p->count_pairs != 0 || out->pairs != nullptr, plan,
-                                    ctx->tuning ? nullptr : &spare, s)));
+        const GatherSpare spare{(double*)rpos_u, (double*)rw_u, N, !ctx->tuning};
+        HIP_OK((launch_gather<R, D>(g, p->mode, p->count_pairs != 0 || out->pairs != nullptr, plan, spare,
+                                    s)));
     }
     return FLA_OK;
 }
@@ -683,7 +683,7 @@ fla_status batch_impl(fla_ctx* ctx, int nsnap, const MeshDev* md, const TrajDev*
             bool general = false;     // any rectilinear axis in the batch
             for (int i = 0; i < nsnap; ++i)
                 for (int a = 0; a < 3; ++a) general = general || md[i].edges[a] != nullptr;
-            const GatherSpare spare{(double*)rpos_u, (double*)rw_u, total};
+            const GatherSpare spare{(double*)rpos_u, (double*)rw_u, total, !ctx->tuning};
             HIP_OK((launch_gather_batch<R, D>(dev_items, nsnap, (int)nwork, (int)nsplit, chunk, count, plan, general, queue,
                                               ncu, spare, q)));
         }

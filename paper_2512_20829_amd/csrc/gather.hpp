@@ -95,7 +95,8 @@ template <typename R, int D> struct GatherWaves { static constexpr int value = D
 // workgroups fit a compute unit instead of one and the binary64 chains of one
 // cover the other's (61 x 47 x 53 cells, 120k trajectories: 382 -> 284 us).  In
 // 2-D, two halves of four waves in place of one tile of two also spread a small
-// mesh over four times the waves (64^2 cells: 87 -> 32 us).
+// mesh over four times the waves (64^2 cells: 87 -> 32 us); whole tiles are
+// staged in the same way and are taken where records are few (whole_tiles).
 template <typename R> __host__ __device__ constexpr int tile_parts(int D, int shape)
 {
     return sizeof(R) == 8 && shape == 0 ? 2 : 1;
@@ -106,7 +107,7 @@ template <typename R> __host__ __device__ constexpr int tile_parts(int D, int sh
 // into the loops, 6.9 instead of 5.0 ms on the 128^3 case; binary64: two where
 // the staging space lets two workgroups in).
 template <typename R, int D, int TP> struct GatherOcc {
-    static constexpr int value = sizeof(R) == 4 || TP == 2 ? 2 : 1;
+    static constexpr int value = sizeof(R) == 4 || TP == 2 || D == 2 ? 2 : 1;
 };
 
 template <typename R, int D, int TP>
@@ -115,7 +116,8 @@ struct GatherLds {
     using R2 = typename V2<R>::T;
     static constexpr int SB = Geo<D>::SB, NA = D + 2;
     static constexpr int NT = TP == 2 ? D - 1 : D;   // axes staged for both halves (split: y, z)
-    static constexpr int NB = TP == 2 ? kWave / 2 : kWave;   // records staged at a time
+    // records staged at a time, lanes that stage one
+    static constexpr int NB = TP == 2 || (D == 2 && sizeof(R) == 8) ? kWave / 2 : kWave, LPR = kWave / NB;
     uint32_t cand[kCap];               // compacted candidate record indices
     R4 tab[NB][NT][SB];                // {s, e} at in-block position l and l + SB
     R2 tabs[NB][TP == 2 ? SB : 1];     // split axis x: {s, e} of the owned half
@@ -141,9 +143,9 @@ __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs
     constexpr int TE = G::TE, SB = G::SB, NSB = G::NSB / TP;
     // positions l of a half tile that this lane takes: all of them, or (two
     // lanes to a record, 32 apart) its half of them
-    constexpr int NL = TP == 2 ? SB / 2 : SB, NP = 2 * NL;
-    const int l0 = TP == 2 ? part * NL : 0;
-    auto whole = [](R v) { return TP == 2 ? fmin(v, __shfl_xor(v, kWave / 2, kWave)) : v; };
+    constexpr int LPR = GatherLds<R, D, TP>::LPR, NL = SB / LPR, NP = 2 * NL;
+    const int l0 = part * NL;
+    auto whole = [](R v) { return LPR == 2 ? fmin(v, __shfl_xor(v, kWave / 2, kWave)) : v; };
     using R4 = typename V4<R>::T;
     using R2 = typename V2<R>::T;
     double x[3] = {P.x, P.y, P.z};
@@ -168,7 +170,7 @@ __device__ __forceinline__ int stage_record(const MeshDev& m, const double (*xcs
             double dm = 0.0;
 #pragma unroll
             for (int p = 0; p < NP; ++p) dm = fmax(dm, fabs(d[p]));
-            if (TP == 2) dm = fmax(dm, __shfl_xor(dm, kWave / 2, kWave));
+            if (LPR == 2) dm = fmax(dm, __shfl_xor(dm, kWave / 2, kWave));
             const double L = m.L[a];
             if (dm > 0.5 * L) {
                 if (dm < L) {
@@ -1134,7 +1136,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& g, const int work,
     constexpr int kGatherWaves = GatherWaves<R, D>::value;
     using G = Geo<D>;
     constexpr int TE = G::TE, SB = G::SB, NSB = G::NSB / TP, C = D + 1, NA = C + 1;
-    constexpr int NB = GatherLds<R, D, TP>::NB, LPR = kWave / NB;   // records a batch, lanes that stage one
+    constexpr int NB = GatherLds<R, D, TP>::NB, LPR = GatherLds<R, D, TP>::LPR;
     constexpr int NT = GatherLds<R, D, TP>::NT;
     constexpr bool kComp = sizeof(R) == 4;
     using R4 = typename V4<R>::T;
@@ -1848,6 +1850,12 @@ template <int MODE> static bool split_pays(int64_t tiles, int64_t records, int n
     return whole <= 1 || (MODE == FLA_DEPOSIT ? 10 * quarters <= 40 * whole : 11 * quarters < 40 * whole);
 }
 
+// 2-D binary64: whole tiles in place of halves where a tile has few records, since
+// each half stages a record's y factors anew and waves of few records idle: 1000^2
+// cells with 2001 records 577 -> 354 us, with 200k 399 -> 339; with 250 and more to a
+// tile the halves' skips and number win, 300^2 and 200k 213 -> 180.
+static bool whole_tiles(int64_t tiles, int64_t records) { return records < 128 * tiles; }
+
 template <int MODE, bool COUNT>
 static void launch_split_batch(const BatchItem* items, int nsnap, int nwork, const GatherSpare& spare, hipStream_t s)
 {
@@ -1882,8 +1890,12 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
         // the XCD counters start at zero (a fill kernel: the launch may be captured)
         hipError_t e = launch_fill_u32(queue, kXcds, 0u, s);
         if (e != hipSuccess) return e;
-        // in 2-D there is no other shape than the first
-        if (D == 2 || shape == 0)
+        if constexpr (D == 2 && sizeof(R) == 8) {
+            if (whole_tiles(nwork, spare.records))
+                launch_batch_shape<R, D, 1>(items, nsnap, first, nwork - first, chunk, count, plan, general, queue, ncu, s);
+            else
+                launch_batch_shape<R, D, 2>(items, nsnap, first, nwork - first, chunk, count, plan, general, queue, ncu, s);
+        } else if (D == 2 || shape == 0)   // in 2-D there is no other shape than the first
             launch_batch_shape<R, D, tile_parts<R>(D, 0)>(items, nsnap, first, nwork - first, chunk, count, plan, general,
                                                           queue, ncu, s);
         else
@@ -1919,7 +1931,7 @@ static bool launch_small(const GatherArgs& g, hipStream_t s)
 }
 
 template <typename R, int D, int TP>
-static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, const GatherSpare* spare,
+static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count, int plan, const GatherSpare& spare,
                                       hipStream_t s)
 {
     const bool general = g.m.edges[0] || g.m.edges[1] || g.m.edges[2];
@@ -1927,16 +1939,16 @@ static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count,
         constexpr int MODE = decltype(modec)::value;
         constexpr bool COUNT = decltype(countc)::value;
         if constexpr (kPlanes<R, D>) {
-            if (spare && split_pays<MODE>(g.m.ntiles, spare->records, g.ncu)) {
+            if (spare.small && split_pays<MODE>(g.m.ntiles, spare.records, g.ncu)) {
                 const unsigned nt = (unsigned)g.m.ntiles;
-                FLA_LAUNCH((k_gather_split<MODE, COUNT>), dim3(nt * 4), dim3(256), 0, s, g, spare->a, spare->b);
-                FLA_LAUNCH((k_split_sum<MODE>), dim3(nt * 2), dim3(256), 0, s, g, (const double*)spare->a,
-                           (const double*)spare->b);
+                FLA_LAUNCH((k_gather_split<MODE, COUNT>), dim3(nt * 4), dim3(256), 0, s, g, spare.a, spare.b);
+                FLA_LAUNCH((k_split_sum<MODE>), dim3(nt * 2), dim3(256), 0, s, g, (const double*)spare.a,
+                           (const double*)spare.b);
                 FLA_LAUNCH((k_gather_overs<R, D, MODE>), dim3(nt), dim3(256), 0, s, g);
                 return hipGetLastError();
             }
         }
-        if (spare && launch_small<R, D, MODE, COUNT>(g, s)) return hipGetLastError();
+        if (spare.small && launch_small<R, D, MODE, COUNT>(g, s)) return hipGetLastError();
         FLA_LAUNCH(k_tile_cost<D>, dim3((unsigned)((g.m.ntiles + 3) / 4)), dim3(256), 0, s, g);
         FLA_LAUNCH(k_tile_order, dim3(kXcds), dim3(1024), 0, s, (const uint32_t*)g.tile_cost, g.m.ntiles * TP, TP,
                    g.order, g.queue);
@@ -1956,11 +1968,14 @@ static hipError_t launch_gather_shape(const GatherArgs& g, int mode, bool count,
 }
 
 template <typename R, int D>
-hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, const GatherSpare* spare,
+hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, const GatherSpare& spare,
                          hipStream_t s)
 {
     if (g.m.ntiles <= 0) return hipSuccess;
     const int plan = plan_code % kGatherPlans, shape = plan_code / kGatherPlans;
+    if constexpr (D == 2 && sizeof(R) == 8)
+        if (whole_tiles(g.m.ntiles, spare.records))
+            return launch_gather_shape<R, D, 1>(g, mode, count, plan, spare, s);
     // in 2-D there is no other shape than the first
     if (D == 2 || shape == 0) return launch_gather_shape<R, D, tile_parts<R>(D, 0)>(g, mode, count, plan, spare, s);
     return launch_gather_shape<R, D, tile_parts<R>(D, D == 3)>(g, mode, count, plan, spare, s);

@@ -4,7 +4,7 @@
 
 namespace flp {
 
-template hipError_t launch_gather<float, 3>(const GatherArgs&, int, bool, int, const GatherSpare*, hipStream_t);
+template hipError_t launch_gather<float, 3>(const GatherArgs&, int, bool, int, const GatherSpare&, hipStream_t);
 template hipError_t launch_gather_batch<float, 3>(const BatchItem*, int, int, int, int, bool, int, bool, uint32_t*, int,
                                              const GatherSpare&, hipStream_t);
 

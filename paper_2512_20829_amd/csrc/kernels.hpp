@@ -47,10 +47,13 @@ hipError_t launch_max_class_batch(const BatchItem* items, int nsnap, const uint3
                                   unsigned long long* stats, hipStream_t s);
 // Persistent gather over the work items of a batch; queue holds kXcds
 // counters of workspace (zeroed by the launcher), ncu the compute units.
-// Memory that the gather may use: the unsorted records, `records` double4 each.
+// Memory that the gather may use (the unsorted records, `records` double4 each),
+// and whether a mesh whose parts all have a workgroup at once may take the
+// launches that no plan code changes (not while these are timed).
 struct GatherSpare {
     double *a, *b;
     int64_t records;
+    bool small;
 };
 // records a tile from which four workgroups share it (k_gather_split), and the spare
 // ones that hold their sums
@@ -132,10 +135,8 @@ constexpr int same_plan_code(int dim, bool f64, int code)
     if (!f64) return plan <= 1 ? 0 : plan;
     return shape == 0 && plan == 3 ? 2 : code;
 }
-// spare: a mesh whose parts all have a workgroup at once may take the launches that
-// no plan code changes; null: the one that the plan codes differ in
 template <typename R, int D>
-hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, const GatherSpare* spare,
+hipError_t launch_gather(const GatherArgs& g, int mode, bool count, int plan_code, const GatherSpare& spare,
                          hipStream_t s);
 
 // PSI-CELL
