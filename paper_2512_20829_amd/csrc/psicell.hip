@@ -560,7 +560,15 @@ __global__ __launch_bounds__(NT) void k_psi_reduce(PsiArgs a)
 #pragma unroll
         for (int u = 0; u < kPsiUnrollReduce; ++u) {
             const int64_t sl = s0 + (int64_t)u * blockDim.x;
-            rec[u] = bucket[sl < end ? sl : end - 1];   // no branch between the loads
+            if (W == 1) {
+                rec[u] = bucket[sl < end ? sl : end - 1];   // no branch between the loads
+            } else {
+                // the branches keep the three loads of a 40-byte record together: in
+                // any order its lines are fetched again (40^2 cells and 6M particles
+                // 3.52 -> 4.36 ms)
+                if (sl < end) rec[u] = bucket[sl];
+                else rec[u].loc = kPsiSkip;
+            }
         }
 #pragma unroll
         for (int u = 0; u < kPsiUnrollReduce; ++u) {
