@@ -165,6 +165,8 @@ struct PsiArgs {
     int binlog;                  // log2 tiles per bin: kPsiTilesPerBinLog, or 0 when direct
     int direct;                  // the scatter writes the tile buckets itself (bins are tiles; no tile pass)
     int nsplit;                  // workgroups per bin in the tile pass; of the whole CIC reduction
+    int64_t piece;               // CIC reduction: one workgroup per tile, or part of one of more
+                                 // records than this (0: nsplit equal shares of all records)
     unsigned int* binhist;       // pnbins * nblocks + 1, scanned in place
     unsigned int* tcursor;       // pntiles: next free slot of each tile bucket, or the tiles in
                                  // the order that the reduce takes them (tile_order)

@@ -934,8 +934,9 @@ __global__ __launch_bounds__(kPsiScatterThreads) void k_cic_scatter_sorted(PsiAr
 
 // The tile buckets lie one after another; each workgroup takes an equal share
 // of all records, so that tiles of any population keep every compute unit
-// busy.  Per tile that its share touches, the particles deposit into LDS sums
-// over the tile and its upper halo, which are then added to the global sums.
+// busy; or, where there are few to a tile, a tile or a part of one.  Per tile
+// that its share touches, the particles deposit into LDS sums over the tile and
+// its upper halo, which are then added to the global sums.
 // Channels 0..C-1 carry phi (W words each), channel C the weights (W words,
 // at the scale of the fine word: at most one unit of weight per particle and
 // corner).  BIG: at least kPsiBigCount particles, whose words stay below 2^50.
@@ -966,11 +967,37 @@ __global__ __launch_bounds__(NT) void k_cic_reduce(PsiArgs a)
     const int64_t nbk = a.nblocks;
     auto start = [&](int t) { return (int64_t)a.blockhist[(int64_t)t * nbk]; };
     const int64_t total = start(a.pntiles);
-    const int64_t beg = total * blockIdx.x / gridDim.x, end = total * (blockIdx.x + 1) / gridDim.x;
+    int64_t beg = total * blockIdx.x / gridDim.x, end = total * (blockIdx.x + 1) / gridDim.x;
+    int tile = -1;
+    if (a.piece) {
+        // a tile, or an even part of one of more than `piece` records: workgroup t < ntiles
+        // takes the first part of tile t, the others number the multiples of
+        // `piece` that the record positions pass
+        const int64_t piece = a.piece;
+        int t = blockIdx.x;
+        int64_t j = 0;
+        if (t >= a.pntiles) {
+            const int64_t e = t - a.pntiles;
+            int hi = a.pntiles - 1;
+            for (t = 0; t < hi;) {
+                const int mid = (t + hi) >> 1;
+                if (start(mid + 1) / piece <= e)
+                    t = mid + 1;
+                else
+                    hi = mid;
+            }
+            if (start(t + 1) / piece <= e) return;
+            j = 1 + e - start(t) / piece;
+        }
+        const int64_t s = start(t), n = start(t + 1) - s, parts = n > piece ? 1 + start(t + 1) / piece - s / piece : 1;
+        if (j >= parts) return;
+        beg = s + n * j / parts;
+        end = s + n * (j + 1) / parts;
+        tile = t - 1;
+    }
     const CicRec<R>* bucket = (const CicRec<R>*)a.bucket;
     const MeshDev& m = a.m;
     const int64_t M = m.M;
-    int tile = -1;
     for (int64_t pos = beg; pos < end;) {
         // the tile of record pos: the next one, or by bisection over empty ones
         ++tile;
@@ -1127,7 +1154,7 @@ hipError_t launch_cic(const PsiArgs& a, hipStream_t s)
         const hipError_t e = hipFuncSetAttribute((const void*)k_cic_reduce<R, D, NT, BIG>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_r);
         if (e != hipSuccess) return e;
-        FLA_LAUNCH((k_cic_reduce<R, D, NT, BIG>), dim3(a.nsplit), dim3(NT), lds_r, s, a);
+        FLA_LAUNCH((k_cic_reduce<R, D, NT, BIG>), dim3(a.piece ? (unsigned)(a.pntiles + a.p.count / a.piece) : (unsigned)a.nsplit), dim3(NT), lds_r, s, a);
         return hipSuccess;
     };
     using Large = std::integral_constant<int, 1024>;
