@@ -51,8 +51,8 @@ typedef enum {
 } fla_status;
 
 /* Arithmetic of a call.  FLA_F32: velocities, radii and outputs are binary32
- * and kernel weights are evaluated in binary32 with compensated binary32
- * sums; det J, number density, smoothing length and cell offsets stay in
+ * and kernel weights are evaluated in binary32 with short binary32 partial
+ * sums, added in binary64 (3-D and general meshes) or with compensation (2-D); det J, number density, smoothing length and cell offsets stay in
  * binary64.  FLA_F64: everything in binary64. */
 typedef enum { FLA_F32 = 0, FLA_F64 = 1 } fla_precision;
 

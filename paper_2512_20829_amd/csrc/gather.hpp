@@ -22,9 +22,11 @@
 //    branch per axis);
 //  * every lane then walks the batch over its cells, skipping what a record
 //    reaches nowhere (an exact, wave-uniform skip).
-// Two tile bodies share this frame:
+// Weights beyond the range of the precision are left out of these sums and added
+// afterwards (add_overs).  Two tile bodies share this frame:
 //  * gather_planes (binary32, 3-D): a lane owns a column of cells, and what
-//    depends on z alone is the same on every lane;
+//    depends on z alone is the same on every lane (few tiles of many records:
+//    four workgroups to each, k_gather_split);
 //  * gather_tile (binary64, and 2-D): the tile is split into 2^D sub-blocks
 //    of SB^D cells and lane l owns the cell with in-block coordinates lc(l)
 //    in every sub-block.
@@ -595,8 +597,8 @@ __device__ __forceinline__ void write_cell(const GatherArgs& g, const int64_t li
 // and weights and the next group's LDS words are in flight while the current
 // ones are used.  Against sub-blocks of 4^3 cells with a sum, a compare, a
 // select and two products per pair (half tiles, three waves per SIMD): 2M
-// trajectories on 128^3 cells 4.79 -> 3.75 ms (24.8 TFLOP/s of the 15 flops
-// per included pair), 32.8M on 256^3 279.6 -> 203 ms (39 TFLOP/s).
+// trajectories on 128^3 cells 4.79 -> 3.8 ms (24.5 TFLOP/s of the 15 flops
+// per included pair), 32.8M on 256^3 272 -> 198 ms (40 TFLOP/s).
 //
 // SPLIT: the workgroup takes the chunks of one of those four waves, number
 // `share`, and writes its sums of the tile to `part` (k_split_sum adds them).  Its
@@ -1912,7 +1914,7 @@ hipError_t launch_gather_batch(const BatchItem* items, int nsnap, int nwork, int
 // each scans and stages the same candidates as one would and evaluates its own
 // planes or sub-blocks of them, so the sums keep their order and their bits.
 // Whole calls with and without: 64^2 cells in binary64 107 -> 93 us, in
-// binary32 140 -> 111; 32^3 in binary32 with 100k trajectories 391 -> 343.
+// binary32 140 -> 111.  (Binary32 3-D tiles of many records: split_pays.)
 // A share skips as finely as there is, and shape 0 has the most workgroups, so
 // plan codes make no difference here.
 template <typename R, int D, int MODE, bool COUNT>

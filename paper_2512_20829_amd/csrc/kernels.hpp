@@ -191,7 +191,7 @@ template <typename R> struct PsiWords { static constexpr int value = sizeof(R) =
 constexpr int kPsiMaxTiles = 16384;   // LDS histogram of the count pass <= 64 KiB
 constexpr int kPsiTilesPerBinLog = 6;
 constexpr int kPsiTilesPerBin = 1 << kPsiTilesPerBinLog;    // tiles per bin of the first partition
-constexpr int kPsiMaxBins = 512;       // bins of the scatter: two per thread in its bin scans
+constexpr int kPsiMaxBins = 512;       // bins of the scatter: one per thread in its bin scans
 static_assert(kPsiMaxTiles / kPsiTilesPerBin <= kPsiMaxBins, "the bins of the tile partition must fit the scatter");
 constexpr int kPsiMaxCellsPerTile = 1024;  // LDS sums of the reduce pass <= 36 KiB
 constexpr int kPsiDirectThreads = 1024;    // threads of a reduce workgroup over one large tile

@@ -222,7 +222,7 @@ __device__ inline unsigned int wave_exclusive_sum(unsigned int v, unsigned int& 
 }
 
 // First partition: each block takes its contiguous range of particles in
-// rounds of 256 U, forms their records, orders a round's records by bin in
+// rounds of kPsiScatterThreads U, forms their records, orders a round's records by bin in
 // LDS (counting sort) and writes them out bin by bin, so a round gives one
 // contiguous run of records per bin and the stores are coalesced.  The
 // slots come from the scanned per-block bin counts of the count pass (a

@@ -213,14 +213,15 @@ hipError_t radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, 
 // (first position of every bucket b in [0, nb]) and the largest non-empty class
 // in one launch instead of the six or more of the passes above and two: 4096
 // keys of 9 bits take 10 us, in their own launches they took 49.  Bound by the
-// chain of its steps: one workgroup, two passes.
+// chain of its steps: one workgroup, two passes.  Named for the scatter that it
+// does in LDS and the bounds that it writes.
 // Each wave keeps 64 K consecutive items in order; a pass ranks them by ballots
 // and a running count per wave and digit, scans the counts digit-major and
 // moves the items in LDS.
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave;
 constexpr int kSmallBuckets = 1 << 14;
 template <int K>
-__global__ __launch_bounds__(kSmallThreads) void k_radix_scatter_small(uint32_t* keys, uint32_t* vals, int n, int bits, int db,
+__global__ __launch_bounds__(kSmallThreads) void k_radix_scatter_bounds(uint32_t* keys, uint32_t* vals, int n, int bits, int db,
                                                             uint32_t nb, int per_class, uint32_t* bstart,
                                                             unsigned long long* max_class)
 {
@@ -336,7 +337,7 @@ hipError_t launch_sort_small(uint32_t* keys, uint32_t* vals, int64_t n, int key_
     const int passes = (key_bits + 7) / 8, db = passes > 0 ? (key_bits + passes - 1) / passes : 1;
     auto run = [&](auto items) {
         constexpr int K = decltype(items)::value;
-        FLA_LAUNCH((k_radix_scatter_small<K>), dim3(1), dim3(kSmallThreads), 0, s, keys, vals, (int)n, key_bits, db, nb,
+        FLA_LAUNCH((k_radix_scatter_bounds<K>), dim3(1), dim3(kSmallThreads), 0, s, keys, vals, (int)n, key_bits, db, nb,
                    per_class, bstart, max_class);
     };
     if (n <= kSmallThreads)
